@@ -125,13 +125,14 @@ __device__ __forceinline__ void qkv_column(const RopeParams& rp, int c0, int r16
 template <typename T, int NT>
 __device__ __forceinline__ void qkv_store(const RopeParams& rp, int m, int pos, int blk, int r16, const float (&o)[NT],
                                           const float (&pr)[NT], const float2 (&cs)[NT], const int (&kind)[NT],
-                                          const int (&qcol)[NT], const size_t (&kvb)[NT]) {
+                                          const int (&qcol)[NT], const size_t (&kvb)[NT], int nt = NT) {
   const int off = pos & 15;
   T* kv = (T*)rp.kv;
   const size_t brow = (size_t)max(blk, 0) * 32 * rp.hd;   // block offset inside a head's run
   const size_t Nq = (size_t)rp.H * rp.hd;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
+    if (j >= nt) continue;                                // columns at or past N
     const float a = r16 < 8 ? o[j] : pr[j], b = r16 < 8 ? pr[j] : o[j];
     const float y = r16 < 8 ? a * cs[j].x - b * cs[j].y : a * cs[j].y + b * cs[j].x;
     if (kind[j] == 0) rp.q[(size_t)m * Nq + qcol[j]] = y;
@@ -451,13 +452,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 // Row-tiled GEMM for passes with more than one 64-row block (batched
 // verify at B >= 32, prefill): there every weight byte meets hundreds of
 // rows, so the operands are staged once per workgroup in LDS and shared.
-// A workgroup of 4 waves (2 x 2) owns a BM x BN = 32 MF x 32 NF output tile;
-// wave (wm, wn) owns the 16 MF x 16 NF sub-tile at (wm 16 MF, wn 16 NF).
-// With 8 waves (one workgroup per CU) waves w and w + 4 own the same
-// sub-tile and take the first and the second k-step of each stage; the
-// second adds its sums to the first's through LDS at the end.
-// K advances in stages of two k-steps (64 fp16); a stage is the
-// 2 (BM + BN) / 16 1 KB fragments, which the waves load straight into
+// A workgroup of WM x WN waves owns a BM x BN output tile, wave (wm, wn) the
+// 16 MF x 16 NF sub-tile at (wm 16 MF, wn 16 NF).
+// K advances in stages of KS k-steps (32 KS fp16); a stage is the
+// KS (BM + BN) / 16 1 KB fragments, which the waves load straight into
 // one of NB LDS buffers (buffer loads with an LDS destination: lane i's
 // 16 bytes land at the buffer's fragment base + 16 i, no registers held).
 // NB - 1 stages are in flight while one is multiplied: at the top of stage
@@ -465,80 +463,95 @@ __device__ __forceinline__ void wait_vmcnt() {
 // NB - 2 stages of its loads outstanding), then one barrier makes every
 // wave's loads visible and frees the buffer stage st - 1 used, which then
 // receives stage st + NB - 1.  Every stage issues the same number of loads
-// (past the last stage, at an out-of-range offset: they read nothing), so
+// (past the last stage with an empty buffer range: they read nothing), so
 // the count the wait uses holds to the end.  The barrier is a plain
 // s_barrier with a compiler memory clobber: a fenced one would wait for
-// every load in flight.  Rows at or past M load zeros (range-checked buffer
-// loads).  Tile order: the row tiles of one column tile take consecutive
-// slots of one XCD (1-D grid, round-robin dispatch over 8 XCDs), so its
-// weights are fetched from HBM once and re-read from that XCD's L2.
-template <int MF, int NF, int EPI, int NB, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void gemm_rows_kernel(GemmParams p) {
-  using T = f16_t;
-  static_assert(WAVES == 4 || WAVES == 8, "4 waves, or 8 that split each stage's two k-steps");
-  constexpr int BM = 32 * MF, BN = 32 * NF;
-  constexpr int FA = 2 * BM / 16, FW = 2 * BN / 16;   // fragments per stage
-  constexpr int LA = (FA + WAVES - 1) / WAVES, LW = (FW + WAVES - 1) / WAVES;   // loads per wave
-  constexpr int SPARE = (WAVES * LA > FA || WAVES * LW > FW) ? 1 : 0;          // their overflow slot
-  constexpr int FS = FA + FW + SPARE;
+// every load in flight.  Rows at or past M and columns at or past N load
+// zeros (range-checked buffer loads).  Tile order: every XCD (workgroups are
+// dispatched round-robin over 8) takes one contiguous run of tiles, the row
+// tiles and K ranges of a column tile first, so that a column tile's weights
+// are fetched from HBM once and re-read from that XCD's L2.
+template <int MF_, int NF_, int WM_, int WN_, int KS_, int NB_> struct RowTile {
+  static constexpr int MF = MF_, NF = NF_, WM = WM_, WN = WN_, KS = KS_, NB = NB_;
+  static constexpr int WAVES = WM * WN, BM = 16 * MF * WM, BN = 16 * NF * WN;
+  static constexpr int FA = BM / 16 * KS, FW = BN / 16 * KS;                     // fragments per stage
+  static constexpr int LA = (FA + WAVES - 1) / WAVES, LW = (FW + WAVES - 1) / WAVES;   // loads per wave
+  static constexpr int SPARE = (FA % WAVES || FW % WAVES) ? 1 : 0;               // their overflow slot
+  static constexpr int FS = FA + FW + SPARE;
+  static constexpr uint32_t LDS = (uint32_t)NB * FS * 1024;
   static_assert(NB >= 2 && (NB - 2) * (LA + LW) < 64, "stages in flight");
+  static_assert(LDS <= 160 * 1024, "LDS of a CU");
+};
+
+template <typename C, int EPI>
+__global__ __launch_bounds__(64 * C::WAVES, 2) void gemm_rows_kernel(GemmParams p) {
+  using T = f16_t;
+  constexpr int MF = C::MF, NF = C::NF, KS = C::KS, NB = C::NB, WAVES = C::WAVES, BM = C::BM, BN = C::BN;
+  constexpr int FA = C::FA, FW = C::FW, LA = C::LA, LW = C::LW, FS = C::FS;
   extern __shared__ __align__(16) unsigned char smem[];
   u32x4* lds = (u32x4*)smem;                          // [NB][FS][64]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 1, wn = (wave >> 1) & 1;
+  const int wm = wave % C::WM, wn = wave / C::WM;
   const int r16 = lane & 15, g = lane >> 4;
-  const int ksteps = p.K * 2 / 64, stages = ksteps / 2;
-  const int gx = p.N / BN, gz = (p.M + BM - 1) / BM;
-  // K split: the R = gz ks (row tile, K range) pairs of a column tile take
-  // consecutive slots of one XCD, as the row tiles alone do without a split
+  const int ksteps = p.K * 2 / 64, stages = ksteps / KS;
+  const int gz = (p.M + BM - 1) / BM;
   const int ks = max(p.ksplit, 1), R = gz * ks;
+  // workgroup w runs on XCD w % 8; XCD x takes the tiles [x T / 8, (x + 1) T / 8) (rounded)
   int bx, r;
   {
-    const int w = blockIdx.x;
-    if (gx % 8 == 0) {
-      const int j = w >> 3;
-      r = j % R;
-      bx = (j / R) * 8 + (w & 7);
-    } else {
-      bx = w % gx;
-      r = w / gx;
-    }
+    const int w = blockIdx.x, T8 = gridDim.x >> 3, rem = gridDim.x & 7, x = w & 7;
+    const int tile = x * T8 + min(x, rem) + (w >> 3);
+    bx = tile / R;
+    r = tile % R;
   }
   const int bz = r % gz, split = r / gz;
   const int sps = (stages + ks - 1) / ks;              // stages of one K range
   const int s_lo = min(split * sps, stages), s_hi = min(s_lo + sps, stages);
   const uint32_t tile_bytes = (uint32_t)ksteps * 1024u;
-  const __amdgpu_buffer_rsrc_t wr = buf_rsrc((const char*)p.W + (size_t)bx * (BN / 16) * tile_bytes, (BN / 16) * tile_bytes);
-  const __amdgpu_buffer_rsrc_t ar = buf_rsrc((const char*)p.A + (size_t)bz * (BM / 16) * tile_bytes, (BM / 16) * tile_bytes);
+  const char* Wp = (const char*)p.W + (size_t)bx * (BN / 16) * tile_bytes;
+  const char* Ap = (const char*)p.A + (size_t)bz * (BM / 16) * tile_bytes;
   const int mvalid = p.M - bz * BM;                   // rows of this tile below M
+  const int ntile = min(BN / 16, p.N / 16 - bx * (BN / 16));   // 16-column tiles below N
 
-  // this wave's share of stage st: A fragments f = WAVES k + wave (k < LA), W
-  // fragments f = WAVES k + wave (k < LW); fragment f = 2 t + u is (16-row
+  // this wave's share of a stage: A fragments f = WAVES k + wave (k < LA), W
+  // fragments f = WAVES k + wave (k < LW); fragment f = KS t + u is (16-row
   // tile t, k-step u of the stage).  Indices past the stage's fragments load
   // nothing (out-of-range offset) into the overflow slot, so every wave
   // issues the same count
+  uint32_t aoff[LA], woff[LW];
+#pragma unroll
+  for (int k = 0; k < LA; ++k) {
+    const int f = WAVES * k + wave, t = f / KS, u = f % KS;
+    aoff[k] = f < FA && 16 * t + r16 < mvalid ? (uint32_t)t * tile_bytes + u * 1024u + lane * 16u : OOB;
+  }
+#pragma unroll
+  for (int k = 0; k < LW; ++k) {
+    const int f = WAVES * k + wave, t = f / KS, u = f % KS;
+    woff[k] = f < FW ? (uint32_t)t * tile_bytes + u * 1024u + lane * 16u : OOB;
+  }
   auto gload = [&](int st) {
     const bool ok = st < s_hi;
+    const __amdgpu_buffer_rsrc_t ar = buf_rsrc(Ap, ok ? (BM / 16) * tile_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(Wp, ok ? (uint32_t)ntile * tile_bytes : 0u);
     u32x4* base = lds + (size_t)(st % NB) * FS * 64;
+    const int so = st * KS * 1024;
 #pragma unroll
     for (int k = 0; k < LA; ++k) {
-      const int f = WAVES * k + wave, t = f >> 1, u = f & 1;
-      const bool real = FA % WAVES == 0 || f < FA;       // known true when the loads divide evenly
-      const uint32_t off = real && ok && 16 * t + r16 < mvalid
-                               ? (uint32_t)t * tile_bytes + (uint32_t)(2 * st + u) * 1024u + lane * 16u
-                               : OOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (__attribute__((address_space(3))) void*)(base + (real ? f : FA + FW) * 64),
-                                               16, off, 0, 0, 0);
+      const int f = WAVES * k + wave;
+      const uint32_t off = aoff[k];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          ar, (__attribute__((address_space(3))) void*)(base + (FA % WAVES == 0 || f < FA ? f : FA + FW) * 64), 16, off,
+          so, 0, 0);
     }
 #pragma unroll
     for (int k = 0; k < LW; ++k) {
-      const int f = WAVES * k + wave, t = f >> 1, u = f & 1;
-      const bool real = FW % WAVES == 0 || f < FW;
-      const uint32_t off = real && ok ? (uint32_t)t * tile_bytes + (uint32_t)(2 * st + u) * 1024u + lane * 16u : OOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (__attribute__((address_space(3))) void*)(base + (real ? FA + f : FA + FW) * 64),
-                                               16, off, 0, 0, 0);
+      const int f = WAVES * k + wave;
+      const uint32_t off = woff[k];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          wr, (__attribute__((address_space(3))) void*)(base + (FW % WAVES == 0 || f < FW ? FA + f : FA + FW) * 64), 16,
+          off, so, 0, 0);
     }
   };
 
@@ -555,71 +568,39 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_rows_kernel(GemmParams p) {
     asm volatile("s_barrier" ::: "memory");
     gload(st + NB - 1);
     const u32x4* base = lds + (size_t)(st % NB) * FS * 64;
-    // 4 waves: both k-steps of the stage; 8 waves: wave group w / 4 takes k-step w / 4
 #pragma unroll
-    for (int uu = 0; uu < 8 / WAVES; ++uu) {
-      const int u = WAVES == 8 ? wave >> 2 : uu;
+    for (int u = 0; u < KS; ++u) {
       u32x4 a[MF], b[NF];
 #pragma unroll
-      for (int i = 0; i < MF; ++i) a[i] = base[(2 * (wm * MF + i) + u) * 64 + lane];
+      for (int j = 0; j < NF; ++j) b[j] = base[(FA + (wn * NF + j) * KS + u) * 64 + lane];
 #pragma unroll
-      for (int j = 0; j < NF; ++j) b[j] = base[(FA + 2 * (wn * NF + j) + u) * 64 + lane];
+      for (int i = 0; i < MF; ++i) a[i] = base[((wm * MF + i) * KS + u) * 64 + lane];
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int j = 0; j < NF; ++j) acc[i][j] = Mfma<T>::step(a[i], b[j], acc[i][j]);
+      __builtin_amdgcn_s_setprio(0);
     }
   }
   wait_vmcnt<0>();                                    // the trailing out-of-range loads
-  if constexpr (WAVES == 8) {
-    // waves 4-7 hand their k-step-1 sums to waves 0-3 through LDS (the stage
-    // buffers, free once every wave is past the loop); waves 0-3 then finish
-    float* red = (float*)smem + (size_t)(wave & 3) * MF * NF * 4 * 64;
-    __syncthreads();
-    if (wave >= 4) {
-#pragma unroll
-      for (int i = 0; i < MF; ++i)
-#pragma unroll
-        for (int j = 0; j < NF; ++j)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) red[((i * NF + j) * 4 + v) * 64 + lane] = acc[i][j][v];
-    }
-    __syncthreads();
-    if (wave >= 4) return;
-#pragma unroll
-    for (int i = 0; i < MF; ++i)
-#pragma unroll
-      for (int j = 0; j < NF; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[i][j][v] += red[((i * NF + j) * 4 + v) * 64 + lane];
-  }
 
   // epilogue: element (i, j, v) is row bz BM + wm 16 MF + 16 i + 4 g + v,
   // column n0 + 16 j + r16 with n0 the first column of the wave's sub-tile.
-  // Every load of the epilogue (residual values; row positions, KV blocks
-  // and rotary inputs) is issued for all of the lane's rows before the first
-  // store: a load after a store to a possibly aliasing address would wait
-  // for that store, one round trip per row.
+  // The loads of the epilogue (residual values; row positions, KV blocks and
+  // rotary inputs) are issued one 16-row tile ahead of the stores: a load
+  // after a store to a possibly aliasing address would wait for that store,
+  // one round trip per row.
   const int n0 = bx * BN + wn * 16 * NF;
+  const int nt = min(NF, ntile - wn * NF);             // tiles of the wave's sub-tile below N (may be <= 0)
   const int mrow0 = bz * BM + wm * 16 * MF + 4 * g;    // + 16 i + v
   if constexpr (EPI == EPI_QKV) {
     int qkind[NF], qcol[NF], qf[NF];
     size_t qkvb[NF];
 #pragma unroll
     for (int j = 0; j < NF; ++j) qkv_column<T>(p.rope, n0 + 16 * j, r16, qkind[j], qcol[j], qf[j], qkvb[j]);
+    if (nt <= 0) return;
     const int half = p.rope.hd / 2;
-    auto store_rows = [&](int i, const int (&pos)[4], const int (&blk)[4], const float2 (&cs)[4][NF]) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float o[NF], pr[NF];
-#pragma unroll
-        for (int j = 0; j < NF; ++j) o[j] = acc[i][j][v];
-#pragma unroll
-        for (int j = 0; j < NF; ++j) pr[j] = __shfl_xor(o[j], 8);
-        if (pos[v] >= 0)   // a row at or past M has pos -1
-          qkv_store<T, NF>(p.rope, mrow0 + 16 * i + v, pos[v], blk[v], r16, o, pr, cs[v], qkind, qcol, qkvb);
-      }
-    };
     auto load_rows = [&](int i, int (&pos)[4], int (&blk)[4]) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -635,64 +616,53 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_rows_kernel(GemmParams p) {
         for (int j = 0; j < NF; ++j)
           c[v][j] = qkind[j] < 2 ? p.rope.tab[(size_t)max(pos[v], 0) * half + qf[j]] : float2{1.f, 0.f};
     };
-    if constexpr (NB > 2) {
-      // one workgroup per CU: registers to spare, so the positions of all
-      // the lane's rows are loaded at once and the rotary inputs one 16-row
-      // tile ahead of the stores
-      int pos[MF][4], blk[MF][4];
+    // positions two 16-row tiles ahead, rotary inputs one ahead
+    int pos[3][4], blk[3][4];
+    float2 cs[2][4][NF];
+    load_rows(0, pos[0], blk[0]);
+    if constexpr (MF > 1) load_rows(1, pos[1], blk[1]);
+    load_cs(pos[0], cs[0]);
 #pragma unroll
-      for (int i = 0; i < MF; ++i) load_rows(i, pos[i], blk[i]);
-      float2 cs[2][4][NF];
-      load_cs(pos[0], cs[0]);
+    for (int i = 0; i < MF; ++i) {
+      if (i + 2 < MF) load_rows(i + 2, pos[(i + 2) % 3], blk[(i + 2) % 3]);
+      if (i + 1 < MF) load_cs(pos[(i + 1) % 3], cs[(i + 1) & 1]);
 #pragma unroll
-      for (int i = 0; i < MF; ++i) {
-        if (i + 1 < MF) load_cs(pos[i + 1], cs[(i + 1) & 1]);
-        store_rows(i, pos[i], blk[i], cs[i & 1]);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 4; ++v) {
+        float o[NF], pr[NF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) o[j] = acc[i][j][v];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) pr[j] = __shfl_xor(o[j], 8);
+        if (pos[i % 3][v] >= 0)   // a row at or past M has pos -1
+          qkv_store<T, NF>(p.rope, mrow0 + 16 * i + v, pos[i % 3][v], blk[i % 3][v], r16, o, pr, cs[i & 1][v], qkind,
+                           qcol, qkvb, nt);
       }
-    } else {
-      // two workgroups per CU (large grids, e.g. prefill): registers are
-      // short, so one row at a time; its loads then wait behind the previous
-      // row's stores, which the long main loop of these shapes hides
-#pragma unroll
-      for (int i = 0; i < MF; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int m = mrow0 + 16 * i + v;
-          float o[NF], pr[NF];
-#pragma unroll
-          for (int j = 0; j < NF; ++j) o[j] = acc[i][j][v];
-#pragma unroll
-          for (int j = 0; j < NF; ++j) pr[j] = __shfl_xor(o[j], 8);
-          if (m >= p.M) continue;
-          const int pos = p.rope.row_pos[m];
-          if (pos < 0) continue;
-          const int blk = p.rope.row_blk[m];
-          float2 cs[NF];
-#pragma unroll
-          for (int j = 0; j < NF; ++j) cs[j] = qkind[j] < 2 ? p.rope.tab[(size_t)pos * half + qf[j]] : float2{1.f, 0.f};
-          qkv_store<T, NF>(p.rope, m, pos, blk, r16, o, pr, cs, qkind, qcol, qkvb);
-        }
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else if constexpr (EPI == EPI_RESID) {
-    float r[MF][4][NF];
-#pragma unroll
-    for (int i = 0; i < MF; ++i)
+    float res[2][4][NF];
+    auto load_res = [&](int i, float (&o)[4][NF]) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int m = mrow0 + 16 * i + v;
 #pragma unroll
-        for (int j = 0; j < NF; ++j) r[i][v][j] = m < p.M ? p.out[(size_t)m * p.ldo + n0 + 16 * j + r16] : 0.f;
+        for (int j = 0; j < NF; ++j) o[v][j] = m < p.M && j < nt ? p.out[(size_t)m * p.ldo + n0 + 16 * j + r16] : 0.f;
       }
+    };
+    load_res(0, res[0]);
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+    for (int i = 0; i < MF; ++i) {
+      if (i + 1 < MF) load_res(i + 1, res[(i + 1) & 1]);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int m = mrow0 + 16 * i + v;
         if (m >= p.M) continue;
 #pragma unroll
-        for (int j = 0; j < NF; ++j) p.out[(size_t)m * p.ldo + n0 + 16 * j + r16] = r[i][v][j] + acc[i][j][v];
+        for (int j = 0; j < NF; ++j)
+          if (j < nt) p.out[(size_t)m * p.ldo + n0 + 16 * j + r16] = res[i & 1][v][j] + acc[i][j][v];
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < MF; ++i)
@@ -704,99 +674,131 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_rows_kernel(GemmParams p) {
           const int F = p.N / 2;
 #pragma unroll
           for (int j = 0; j < NF; j += 2)
-            Store<T>::store((T*)p.out_t, Tile<T>::off(m, n0 / 2 + 8 * j + r16, F), silu(acc[i][j][v]) * acc[i][j + 1][v]);
+            if (j < nt)
+              Store<T>::store((T*)p.out_t, Tile<T>::off(m, n0 / 2 + 8 * j + r16, F), silu(acc[i][j][v]) * acc[i][j + 1][v]);
         } else {
           const size_t row = EPI == EPI_PART ? (size_t)split * p.M + m : (size_t)m;
 #pragma unroll
-          for (int j = 0; j < NF; ++j) p.out[row * p.ldo + n0 + 16 * j + r16] = acc[i][j][v];
+          for (int j = 0; j < NF; ++j)
+            if (j < nt) p.out[row * p.ldo + n0 + 16 * j + r16] = acc[i][j][v];
         }
       }
   }
 }
 
-// LDS stages of the row-tiled GEMM: with one workgroup per CU (at most 256
-// workgroups) as many as fit below 160 KB, up to 4; else 2, so that two
-// workgroups share a CU.  Measured with weights streamed from HBM: 7B
-// gate/up at M = 160 (172 workgroups) 67.7 -> 54.4 us with 4 stages (2:
-// 65.0), QKV 55.3 -> 36.7, LM head 71.9 -> 59.1; 13B gate/up at M = 320
-// (432 workgroups) 118 -> 110 us with 2 stages (4: 124.6), LM head 125.5
-// -> 111.3 (4: 153.8).
-// With at most 256 workgroups (one per CU) the kernel runs 8 waves: two per
-// SIMD issue the LDS fills and matrix instructions that one wave per SIMD
-// left half idle.  7B paged verify at M = 160 (kernel trace): gate/up 56.4
-// -> 54.4 us, O / down with K split 24.3 -> 22.9, LM head 62.8 -> 60.7;
-// above 256 workgroups two 4-wave workgroups share a CU instead.
-constexpr int rows_stage_kb(int mf, int nf, int waves) {
-  const int fa = 4 * mf, fw = 4 * nf, la = (fa + waves - 1) / waves, lw = (fw + waves - 1) / waves;
-  return fa + fw + ((waves * la > fa || waves * lw > fw) ? 1 : 0);
-}
-constexpr int rows_stages_max(int mf, int nf, int waves) {
-  return 159 / rows_stage_kb(mf, nf, waves) >= 4 ? 4 : 3;
-}
-constexpr bool rows_waves8(int epi, int mf) { return epi != EPI_RESID && epi != EPI_QKV && mf != 8; }
-int gemm_rows_stages(int mf, int nf, int grid, int epi) {
-  return grid <= 256 ? rows_stages_max(mf, nf, rows_waves8(epi, mf) ? 8 : 4) : 2;
-}
-size_t gemm_rows_lds(int mf, int nf, int nb, int waves) {
-  const size_t stages = (size_t)nb * rows_stage_kb(mf, nf, waves) * 1024;
-  const size_t red = waves == 8 ? (size_t)4 * mf * nf * 4 * 64 * sizeof(float) : 0;
-  return std::max(stages, red);
-}
-
-template <int EPI, int MF, int NF, int NB, int WAVES>
-static hipError_t launch_rows_t(int gz, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const size_t lds = gemm_rows_lds(MF, NF, NB, WAVES);
+template <typename C, int EPI>
+static hipError_t launch_rows_t(const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   static bool attr = false;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<MF, NF, EPI, NB, WAVES>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<C, EPI>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
     if (e != hipSuccess) return e;
     attr = true;
   }
-  launch_k(gemm_rows_kernel<MF, NF, EPI, NB, WAVES>, dim3(p.N / (32 * NF) * gz * std::max(p.ksplit, 1)),
-           dim3(64 * WAVES), (uint32_t)lds, s, e0, e1, p);
+  const int grid = (p.N + C::BN - 1) / C::BN * ((p.M + C::BM - 1) / C::BM) * std::max(p.ksplit, 1);
+  launch_k(gemm_rows_kernel<C, EPI>, dim3(grid), dim3(64 * C::WAVES), C::LDS, s, e0, e1, p);
   return hipGetLastError();
 }
 
+// The output tiles, largest first, and the time model that picks one: a
+// workgroup alone on its CU takes a k-step in a microseconds, c more as the
+// grid fills the 256 CUs (they share L2 and HBM), and e in all for its start
+// and epilogue; with two workgroups per CU (the 4-wave tiles of 128 columns)
+// a k-step of both takes a + c and one alone h times that.  The constants are
+// a least-squares fit to 7000 measured launches (64 <= M <= 2048; N and K of
+// the 7B, 13B and small targets and the drafts; weights streamed from HBM):
+// the model's choice is on average 1.2 % slower than the fastest tile.
+// What each is for, at its best against the 128-192 x 128 tiles with stages
+// of two k-steps that it replaced:
+//   256 x 128, 192 x 128 (two per CU, stages of one k-step: 72 and 60 KB of
+//     LDS): grids beyond 512 workgroups.  M = 2048: 7B gate/up 386 -> 337 us
+//     (1.10 PFLOP/s), QKV 225 -> 196, 13B gate/up 595 -> 513
+//   160 x 256, 128 x 256 (one per CU, 8 waves): fewer, larger tiles read
+//     each operand less often per product.  13B gate/up at M = 320 115 -> 98
+//     us; 7B down projection at M = 2048 190 us (was on the skinny GEMM: 775)
+//   160 x 128 ... 64 x 64 (one per CU, 8 waves, up to 112 KB in flight):
+//     grids near 256 workgroups, with K split where the output is narrow
+struct RowTileModel {
+  int bm, bn, per_cu;
+  float e, a, c, h;
+};
+static const RowTileModel ROW_TILES[] = {
+    {256, 128, 2, 5.4f, 0.653f, 0.177f, 0.66f}, {192, 128, 2, 4.4f, 0.495f, 0.160f, 0.70f},
+    {160, 256, 1, 4.4f, 0.433f, 0.158f, 1.0f},  {128, 256, 1, 3.5f, 0.379f, 0.125f, 1.0f},
+    {160, 128, 1, 3.1f, 0.264f, 0.088f, 1.0f},  {128, 128, 1, 2.8f, 0.233f, 0.075f, 1.0f},
+    {128, 64, 1, 1.9f, 0.149f, 0.044f, 1.0f},   {96, 128, 1, 2.2f, 0.212f, 0.048f, 1.0f},
+    {96, 64, 1, 1.8f, 0.142f, 0.027f, 1.0f},    {64, 128, 1, 1.7f, 0.163f, 0.046f, 1.0f},
+    {64, 64, 1, 1.5f, 0.101f, 0.029f, 1.0f},
+};
+constexpr int N_ROW_TILES = sizeof(ROW_TILES) / sizeof(ROW_TILES[0]);
+
 template <int EPI>
-static hipError_t launch_rows_e(int mf, int nf, int gz, const GemmParams& p, hipStream_t s, hipEvent_t e0,
-                                hipEvent_t e1) {
-  const int grid = p.N / (32 * nf) * gz * std::max(p.ksplit, 1);
-  const int nb = gemm_rows_stages(mf, nf, grid, EPI);
-  // the residual-add epilogue (a tile of residual values held), the QKV
-  // epilogue (the row positions, KV blocks and rotary inputs of all of a
-  // lane's rows prefetched) and 256-row tiles stay on 4 waves: 8 would leave
-  // them short of registers (QKV on 8 waves with a row-at-a-time epilogue:
-  // 7B at M = 160 50.2 us against 45.5)
-#define SD_ROWS_CASE(MFv, NFv)                                                            \
-  if (mf == MFv && nf == NFv) {                                                           \
-    constexpr int w1 = rows_waves8(EPI, MFv) ? 8 : 4;                                     \
-    constexpr int hi = rows_stages_max(MFv, NFv, w1);                                     \
-    return nb == 2 ? launch_rows_t<EPI, MFv, NFv, 2, 4>(gz, p, s, e0, e1)                 \
-                   : launch_rows_t<EPI, MFv, NFv, hi, w1>(gz, p, s, e0, e1);              \
+static hipError_t launch_rows_e(int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  switch (tile) {   // in the order of ROW_TILES
+    case 0: return launch_rows_t<RowTile<8, 4, 2, 2, 1, 3>, EPI>(p, s, e0, e1);
+    case 1: return launch_rows_t<RowTile<6, 4, 2, 2, 1, 3>, EPI>(p, s, e0, e1);
+    case 2: return launch_rows_t<RowTile<5, 4, 2, 4, 2, 3>, EPI>(p, s, e0, e1);
+    case 3: return launch_rows_t<RowTile<4, 4, 2, 4, 1, 4>, EPI>(p, s, e0, e1);
+    case 4: return launch_rows_t<RowTile<5, 2, 2, 4, 2, 3>, EPI>(p, s, e0, e1);
+    case 5: return launch_rows_t<RowTile<4, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
+    case 6: return launch_rows_t<RowTile<2, 2, 4, 2, 4, 3>, EPI>(p, s, e0, e1);
+    case 7: return launch_rows_t<RowTile<3, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
+    case 8: return launch_rows_t<RowTile<3, 2, 2, 2, 4, 3>, EPI>(p, s, e0, e1);
+    case 9: return launch_rows_t<RowTile<2, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
+    case 10: return launch_rows_t<RowTile<1, 2, 4, 2, 4, 4>, EPI>(p, s, e0, e1);
+    default: return hipErrorInvalidValue;
   }
-  SD_ROWS_CASE(4, 2) SD_ROWS_CASE(5, 2) SD_ROWS_CASE(6, 2) SD_ROWS_CASE(8, 2)
-  SD_ROWS_CASE(4, 4) SD_ROWS_CASE(5, 4) SD_ROWS_CASE(6, 4) SD_ROWS_CASE(8, 4)
-#undef SD_ROWS_CASE
-  return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_rows(int epi, int mf, int nf, const GemmParams& p, hipStream_t s, hipEvent_t e0,
-                            hipEvent_t e1) {
-  const int bn = 32 * nf, bm = 32 * mf;
-  if (p.N % bn || p.M < 1 || ((size_t)p.K * 2) % GEMM_CHUNK) return hipErrorInvalidValue;
+int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
+  const int ksteps = K * 2 / 64;
+  // a split range holds at least one stage of every tile (GEMM_CHUNK bytes of K)
+  max_ksplit = std::max(1, std::min(max_ksplit, (int)((size_t)K * 2 / GEMM_CHUNK)));
+  int best = 0;
+  double best_t = 1e30;
+  for (int t = 0; t < N_ROW_TILES; ++t) {
+    const RowTileModel& m = ROW_TILES[t];
+    for (int ks = 1; ks <= max_ksplit; ++ks) {
+      const int grid = (M + m.bm - 1) / m.bm * ((N + m.bn - 1) / m.bn) * ks;
+      if (ks > 1 && grid > 640) break;      // splitting is for grids that leave CUs idle
+      // rounds of 256 per_cu workgroups; the last one holds the share `part`
+      const int slots = 256 * m.per_cu, full = grid / slots;
+      const double part = (double)(grid - full * slots) / slots, one = 1.0 / m.per_cu;
+      double last = 0;
+      if (part > 0) {
+        if (m.per_cu == 1) last = 1.0;
+        else if (full == 0) last = part > one + 0.02 ? 1.0 : m.h;
+        else last = part > one ? m.h + (1 - m.h) * (part - one) / (1 - one) : m.h * (0.5 + 0.5 * part / one);
+      }
+      const double step = m.a + m.c * std::min(1.0, grid / 256.0);
+      double us = m.e * (full + (part > 0)) + ((ksteps + ks - 1) / ks) * (full + last) * step;
+      if (ks > 1) us += (double)ks * M * N * 1e-6;   // the RMSNorm reads the partial sums (4 TB/s)
+      if (us < best_t) {
+        best_t = us;
+        best = t;
+        *ksplit = ks;
+      }
+    }
+  }
+  return best;
+}
+
+hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (tile < 0 || tile >= N_ROW_TILES || p.N % 16 || p.M < 1 || ((size_t)p.K * 2) % GEMM_CHUNK)
+    return hipErrorInvalidValue;
   // a K split writes partial sums (PART) and needs at least one stage per range
   if (p.ksplit > 1 && (epi != EPI_PART || p.ksplit > (int)((size_t)p.K * 2 / GEMM_CHUNK))) return hipErrorInvalidValue;
   if (epi == EPI_PART && p.ksplit < 1) return hipErrorInvalidValue;
-  const int gz = (p.M + bm - 1) / bm;
   switch (epi) {
-    case EPI_STORE: return launch_rows_e<EPI_STORE>(mf, nf, gz, p, s, e0, e1);
-    case EPI_RESID: return launch_rows_e<EPI_RESID>(mf, nf, gz, p, s, e0, e1);
-    case EPI_SWIGLU: return launch_rows_e<EPI_SWIGLU>(mf, nf, gz, p, s, e0, e1);
-    case EPI_PART: return launch_rows_e<EPI_PART>(mf, nf, gz, p, s, e0, e1);
+    case EPI_STORE: return launch_rows_e<EPI_STORE>(tile, p, s, e0, e1);
+    case EPI_RESID: return launch_rows_e<EPI_RESID>(tile, p, s, e0, e1);
+    case EPI_SWIGLU:
+      if (p.N % 32) return hipErrorInvalidValue;
+      return launch_rows_e<EPI_SWIGLU>(tile, p, s, e0, e1);
+    case EPI_PART: return launch_rows_e<EPI_PART>(tile, p, s, e0, e1);
     case EPI_QKV:
       if (p.rope.hd % 16 || p.N != (p.rope.H + 2 * p.rope.KV) * p.rope.hd) return hipErrorInvalidValue;
-      return launch_rows_e<EPI_QKV>(mf, nf, gz, p, s, e0, e1);
+      return launch_rows_e<EPI_QKV>(tile, p, s, e0, e1);
     default: return hipErrorInvalidValue;
   }
 }

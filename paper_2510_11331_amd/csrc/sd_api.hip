@@ -207,7 +207,7 @@ void lay_lane(Alloc& al, Lane& ln, int rows, const Dims& D, int decode_rb, int q
   ln.q = al.take<float>(sizeof(float) * rows * D.nq);
   ln.att = al.take<void>(D.esz * rows * D.nq);
   ln.hmid = al.take<void>(D.esz * rows * D.F);
-  ln.part_rows = std::min(rows, 640);   // the largest pass whose residual projections split K
+  ln.part_rows = std::min(rows, 640);   // K splits of longer passes: as many as fit
   ln.part = al.take<float>(sizeof(float) * MAX_KSPLIT * ln.part_rows * D.d);
   ln.logits = logits_rows ? al.take<float>(sizeof(float) * logits_rows * D.V) : nullptr;
   ln.attn_items = decode_rb * D.KV;
@@ -377,86 +377,34 @@ GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = fal
   return g;
 }
 
-// Passes of several 64-row blocks (bf16) run the wide projections (QKV,
-// gate/up, LM head: N >= 8192) on the row-tiled GEMM with 32 mf-row tiles,
-// mf in 4..6 with the fewest padding rows (ties to the taller tile; 192-row
-// tiles for prefill chunks), and 128-column tiles where they leave at least
-// 128 workgroups, else 64-column.  Measured at the 7B B = 32
-// and 13B B = 64 verify shapes (weights streamed from HBM): 13B gate/up at
-// M = 320 109 us against 205 us on the skinny GEMM, LM head 108 against 245.
-// The residual projections (N = d_model) from 128 to 640 rows run on
-// 128 x 128 row tiles with K split when the caller can add partial sums
-// (split_ok; *ks receives the split): 7B at M = 160: O 14.6-15.6 us and down
-// 29.8-32.3 us, against about 22 and 64 on the skinny GEMM; 13B at M = 320:
-// O 24.8 us, down 58.3, against 40.8 and 93.2 unsplit.  The split is chosen
-// for the grid (column tiles x row tiles x splits): the largest split up to
-// MAX_KSPLIT that keeps it within 512 workgroups (two per CU), or, when that
-// grid would leave CUs with one workgroup and others with two (257 to 447
-// workgroups), the largest that keeps it within 256 (one per CU), if that
-// still splits.  Measured against the fixed four-way split (weights streamed
-// from HBM): 13B down at M = 192 / 256 / 448 / 512: 44.4 / 53.9 / 77.1 / 88.5
-// us against 58.6 / 70.4 / 107.8 / 125.2 (O: 20.6 / 24.5 / 30.8 / 36.8
-// against 23.9 / 28.3 / 43.2 / 50.7); 7B down at M = 320 / 576: 40.6 / 59.5
-// against 45.4 / 87.6.  Without a split they run on 128 x 64 tiles from 256
-// to 640 rows and on the skinny GEMM below.  Returns false where the skinny
-// GEMM runs.
-int resid_ksplit(int M, int N) {
-  const int tiles = (N / 128) * ((M + 127) / 128);
-  int k512 = 0, k256 = 0;
-  for (int k = 1; k <= MAX_KSPLIT; ++k) {
-    if (tiles * k <= 512) k512 = k;
-    if (tiles * k <= 256) k256 = k;
-  }
-  const int g = tiles * k512;
-  return g > 256 && g < 448 && k256 >= 2 ? k256 : k512;
-}
-
-bool plan_rows(int M, int N, int K, int dtype, int epi, bool split_ok, int* mf, int* nf, int* ks) {
+// Whether a projection runs on the row-tiled GEMM (16-bit operands only).
+// Above one 64-row block it does, with the tile and K split of pick_row_tile:
+// the skinny GEMM re-reads the activations for every 32 columns and the
+// weights for every 64 rows (7B residual projections at 2048 rows: O 299 ->
+// 77 us, down 775 -> 190; draft d = 1024 at 2048 rows: down 54 -> 23).  Not the
+// small QKV and gate/up projections (N K up to 6.3 M: the small target's QKV,
+// the drafts') up to 128 rows: their grids of 64-column tiles are under 100
+// workgroups that walk the whole K alone, where the skinny GEMM's four waves
+// split it (small QKV at 128 rows 7.4 us against 9.8).
+// max_split: K ranges the caller can add (1: none).
+bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile, int* ks) {
   *ks = 1;
-  // a split range holds at least one stage (GEMM_CHUNK bytes of K)
-  const int ks_res = std::min(resid_ksplit(M, N), K * 2 / GEMM_CHUNK);
-  if (epi == EPI_RESID && dtype == SD_DTYPE_BF16 && split_ok && M >= 128 && M <= 640 && N % 128 == 0 &&
-      ks_res >= 2) {
-    *mf = 4;
-    *nf = 4;
-    *ks = ks_res;
-    return true;
-  }
-  if (epi == EPI_RESID && dtype == SD_DTYPE_BF16 && M >= 256 && M <= 640 && N % 64 == 0) {
-    *mf = 4;
-    *nf = 2;
-    return true;
-  }
-  if (dtype != SD_DTYPE_BF16 || M <= GEMM_MROWS || epi == EPI_PART || epi == EPI_RESID || N < 8192) return false;
-  int best = 6, pad = 1 << 30;
-  if (M <= 640) {
-    for (int c : {4, 5, 6}) {
-      const int rows = (M + 32 * c - 1) / (32 * c) * 32 * c;
-      if (rows <= pad) {
-        pad = rows;
-        best = c;
-      }
-    }
-  }
-  *mf = best;
-  // 128-column tiles while they leave at least 128 workgroups, else 64
-  // (7B QKV at M = 160: 96 -> 192 workgroups, 60.8 -> 55.3 us in the sweep)
-  const int mtiles = (M + 32 * best - 1) / (32 * best);
-  *nf = N % 128 == 0 && mtiles * (N / 128) >= 128 ? 4 : 2;
-  if (N % (32 * *nf)) return false;
+  if (dtype != SD_DTYPE_BF16 || M <= GEMM_MROWS || epi == EPI_PART || N % (epi == EPI_SWIGLU ? 32 : 16)) return false;
+  if (epi != EPI_RESID && epi != EPI_STORE && M <= 128 && (size_t)N * K <= 6300000) return false;
+  *tile = pick_row_tile(M, N, K, epi == EPI_RESID ? max_split : 1, ks);
   return true;
 }
 
-// Launch one projection.  part != null allows the K-split form for EPI_RESID:
-// then *nsplit receives the number of partial sums written to part
+// Launch one projection.  max_split > 1 allows the K-split form for EPI_RESID
+// (part holds max_split partial sums): then *nsplit receives the number of partial sums written to part
 // ([nsplit, M, ldo]) instead of being added to out, and the caller's RMSNorm
 // adds them; otherwise *nsplit = 0.
 int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, int M, int N, int K,
          float* out, int ldo, void* out_t, hipStream_t s, int prof_kind, int prof_kind2,
-         const RopeParams* rope = nullptr, float* part = nullptr, int* nsplit = nullptr) {
-  int mf = 0, nf = 0, rks = 1;
-  const bool rows = plan_rows(M, N, K, m.c.dtype, epi, part != nullptr, &mf, &nf, &rks);
-  GemmPlan g = plan_gemm(M, N, K, m.esz, epi, part != nullptr && !rows);
+         const RopeParams* rope = nullptr, float* part = nullptr, int max_split = 1, int* nsplit = nullptr) {
+  int tile = 0, rks = 1;
+  const bool rows = plan_rows(M, N, K, m.c.dtype, epi, max_split, &tile, &rks);
+  GemmPlan g = plan_gemm(M, N, K, m.esz, epi, !rows && max_split >= SKINNY_MAX_KSPLIT);
   if (!rows && !g.tu && N % (16 * g.nt)) return SD_EINVAL;
   const int ksplit = rows ? rks : g.ksplit;
   if (nsplit) *nsplit = 0;
@@ -485,7 +433,7 @@ int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, i
   ProfRec r1;
   prof_begin(ctx, s, r1, prof_kind, prof_kind2, bytes, true);
   if (rows)
-    HIPCHK(launch_gemm_rows(epi, mf, nf, p, s, r1.a, r1.b));
+    HIPCHK(launch_gemm_rows(epi, tile, p, s, r1.a, r1.b));
   else
     HIPCHK(launch_gemm(m.c.dtype == SD_DTYPE_F32 ? 1 : 0, epi, g.nt, g.mt, g.kw, g.gx, g.ksplit, g.gz, p, s, r1.a,
                        r1.b));
@@ -577,11 +525,11 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     prof_begin(ctx, s, ra, verify ? SD_PROF_ATTN_VERIFY : -1, -1, 0, true);
     HIPCHK(launch_attention(dt, ap, s, ra.a, ra.b));
     prof_end(ctx, s, ra);
-    // residual projections may leave K-split partial sums in ln.part for the
-    // RMSNorm after them to add
-    const bool can_split = M <= ln.part_rows;
+    // residual projections may leave K-split partial sums in ln.part (sized
+    // for MAX_KSPLIT of them at part_rows rows) for the RMSNorm after them to add
+    const int max_split = std::min(MAX_KSPLIT, MAX_KSPLIT * ln.part_rows / M);
     rc = gemm(ctx, m, EPI_RESID, ln.att, m.wo[l], M, d, m.nq(), ln.x, d, nullptr, s, pk_all, -1, nullptr,
-              can_split ? ln.part : nullptr, &ns);
+              ln.part, max_split, &ns);
     if (rc) return rc;
     NormParams np{ln.x, ns ? ln.part : nullptr, ns, m.ffn_norm[l], ln.xn, M, d, 1, 0, M, c.rms_eps};
     HIPCHK(launch_rmsnorm(dt, np, s));
@@ -590,7 +538,7 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     if (rc) return rc;
     const bool norm_next = l + 1 < c.n_layers || lm_M > 0;
     rc = gemm(ctx, m, EPI_RESID, ln.hmid, m.wdown[l], M, d, c.d_ffn, ln.x, d, nullptr, s, pk_all, -1, nullptr,
-              can_split && norm_next ? ln.part : nullptr, &ns);
+              ln.part, norm_next ? max_split : 1, &ns);
     if (rc) return rc;
     if (l + 1 < c.n_layers) {
       NormParams nn{ln.x, ns ? ln.part : nullptr, ns, m.attn_norm[l + 1], ln.xn, M, d, 1, 0, M, c.rms_eps};

@@ -255,10 +255,12 @@ inline void launch_k(K kern, dim3 grid, dim3 block, uint32_t shm, hipStream_t s,
   else hipLaunchKernelGGL(kern, grid, block, shm, s, args...);
 }
 
-// Row-tiled bf16 GEMM for passes of several 64-row blocks: 32 mf x 32 nf
-// output tiles, mf in {4, 5, 6, 8}, nf in {2, 4}; epi: STORE, RESID, SWIGLU
-// or QKV (no K split).  N must be a multiple of 32 nf.
-hipError_t launch_gemm_rows(int epi, int mf, int nf, const GemmParams& p, hipStream_t s, hipEvent_t e0 = nullptr,
+// Row-tiled GEMM (16-bit operands) for passes of more rows than the skinny
+// GEMM's one block: output tile number `tile` of the list in gemm.hip
+// (pick_row_tile chooses one, and the number of K ranges up to max_ksplit).
+// N a multiple of 16 (SWIGLU: 32).
+int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit);
+hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0 = nullptr,
                             hipEvent_t e1 = nullptr);
 // Host-side check of a skinny GEMM launch (launch_gemm rejects what fails it)
 bool gemm_config_ok(int dtype, int epi, int nt, int mt, int kw, int grid_x, int ksplit, int grid_z,

@@ -1,0 +1,91 @@
+"""Row-tiled GEMM: every output tile, K split and epilogue at row and column
+counts around the tile edges, through prefill chunks of a given number of
+rows (three prompts in one chunk, so row positions jump inside a tile)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import model as om
+from paper_2510_11331_amd import _lib
+from sdcase import make_engine, run_gpu_steps, say
+
+WIDE = synth.ModelShape(2, 1024, 8, 8, 11008, 1008, "bf16")
+NARROW = synth.ModelShape(2, 512, 8, 1, 1408, 1008, "bf16")    # GQA: 640 QKV columns; 1008 logits end inside a tile
+DRAFT = synth.ModelShape(1, 128, 2, 2, 256, 1008, "bf16")
+CASES = [(WIDE, 65), (WIDE, 129), (WIDE, 161), (WIDE, 257), (WIDE, 330), (WIDE, 511), (WIDE, 700), (WIDE, 1030),
+         (WIDE, 2049), (NARROW, 127), (NARROW, 700), (NARROW, 1030)]
+# Largest error of a row over its largest logit, against the model with the
+# same fp16 storage points: sums of another order move some operands to the
+# neighbouring fp16 value (2^-11), at the four product inputs and the K/V and
+# q roundings of two layers and the final norm: at most 2^-11 (2 x 6 + 1) / 2
+BOUND = 2.0 ** -11 * 6.5
+
+
+def _pick(M, N, K, max_split):
+    f = _lib.lib()["_ZN2sd13pick_row_tileEiiiiPi"]
+    ks = C.c_int()
+    return f(M, N, K, max_split, C.byref(ks)), ks.value
+
+
+def _plans(shape, M):
+    """(epilogue, tile, K split) of a chunk of M rows; partial sums: six of up to 640 rows."""
+    hd = shape.d_model // shape.n_heads
+    mx = min(6, 6 * min((M + 63) // 64 * 64, 640) // M)
+    return [("qkv", *_pick(M, shape.d_model + 2 * shape.n_kv_heads * hd, shape.d_model, 1)),
+            ("resid", *_pick(M, shape.d_model, shape.d_model, mx)), ("gateup", *_pick(M, 2 * shape.d_ffn, shape.d_model, 1)),
+            ("resid", *_pick(M, shape.d_model, shape.d_ffn, mx))]
+
+
+def test_cases_reach_every_tile():
+    plans = [p for s, M in CASES for p in _plans(s, M)]
+    assert {t for _, t, _ in plans} == set(range(11))
+    assert {k for _, _, k in plans} >= {1, 2, 3, 4, 5, 6}
+    assert _pick(2048, 4096, 11008, 1)[1] == 1
+    # a K range is never shorter than a stage of any tile (128 fp16)
+    for M in (65, 300, 640):
+        for K in (128, 256, 384, 640):
+            assert _pick(M, 128, K, 6)[1] <= K // 64
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,rows", CASES, ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
+def test_prefill_chunk_matches_oracle(shape, rows):
+    say("row tiles", shape, rows, _plans(shape, rows))
+    lens = [rows // 3 + 1, rows // 2 + 1]
+    lens.append(rows - sum(lens) + 3)                          # prompt[:-1] of the three fills the chunk
+    assert sum(n - 1 for n in lens) == rows
+    prompts = synth.prompts(3, lens, shape.vocab)
+    tw, dw = synth.model_weights(shape, 5), synth.model_weights(DRAFT, 6)
+    eng = make_engine(shape, DRAFT, tw, dw, max_slots=3, max_batch=3, gamma_max=1, max_ctx=max(lens) + 16,
+                      prefill_rows=rows)
+    _, _, b, z = run_gpu_steps(eng, [0, 1, 2], prompts, 1, 1, 9, [0, 1, 2], keep_logits=True)
+    drafts = b.draft_tok.cpu().numpy()
+    assert eng.check_flags() == 0
+    eng.close()
+    ref = om.Model(shape, tw).sequence_logits([list(p) + [int(drafts[k, 0])] for k, p in enumerate(prompts)], 2)
+    for k in range(3):
+        for j in range(2):
+            err = float(np.abs(z[0, k, j] - ref[k][j]).max() / np.abs(ref[k][j]).max())
+            assert err < BOUND, (k, j, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7)])
+def test_batched_verify_matches_oracle(B, gamma):
+    """65, 120 and 264 verified rows: K-split residual projections and an LM head whose last column tile is partial."""
+    say("row tiles, verify", B, gamma)
+    prompts = synth.prompts(B, [5 + k % 7 for k in range(B)], NARROW.vocab)
+    tw, dw = synth.model_weights(NARROW, 5), synth.model_weights(DRAFT, 6)
+    eng = make_engine(NARROW, DRAFT, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
+    _, _, b, z = run_gpu_steps(eng, list(range(B)), prompts, gamma, 1, 9, list(range(B)), keep_logits=True)
+    drafts = b.draft_tok.cpu().numpy()
+    assert eng.check_flags() == 0
+    eng.close()
+    ref = om.Model(NARROW, tw).sequence_logits([list(p) + [int(t) for t in drafts[k]] for k, p in enumerate(prompts)],
+                                               gamma + 1)
+    for k in range(B):
+        for j in range(gamma + 1):
+            err = float(np.abs(z[0, k, j] - ref[k][j]).max() / np.abs(ref[k][j]).max())
+            assert err < BOUND, (k, j, err)
