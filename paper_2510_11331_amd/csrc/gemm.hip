@@ -102,6 +102,7 @@ template <typename T>
 __device__ __forceinline__ void qkv_column(const RopeParams& rp, int c0, int r16, int& kind, int& qcol, int& f,
                                            size_t& kvb) {
   const int hd = rp.hd, half = hd / 2, Nq = rp.H * hd, Nqk = Nq + rp.KV * hd;
+  c0 += rp.col0;
   kind = c0 < Nq ? 0 : c0 < Nqk ? 1 : 2;
   qcol = 0;
   f = 0;
@@ -783,6 +784,12 @@ int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
   return best;
 }
 
+// columns col0 .. of the fused projection, whole heads
+static bool qkv_shape_ok(const GemmParams& p) {
+  const RopeParams& r = p.rope;
+  return r.hd % 16 == 0 && r.col0 >= 0 && r.col0 % r.hd == 0 && p.N == (r.H + 2 * r.KV) * r.hd - r.col0;
+}
+
 hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (tile < 0 || tile >= N_ROW_TILES || p.N % 16 || p.M < 1 || ((size_t)p.K * 2) % GEMM_CHUNK)
     return hipErrorInvalidValue;
@@ -797,7 +804,7 @@ hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t 
       return launch_rows_e<EPI_SWIGLU>(tile, p, s, e0, e1);
     case EPI_PART: return launch_rows_e<EPI_PART>(tile, p, s, e0, e1);
     case EPI_QKV:
-      if (p.rope.hd % 16 || p.N != (p.rope.H + 2 * p.rope.KV) * p.rope.hd) return hipErrorInvalidValue;
+      if (!qkv_shape_ok(p)) return hipErrorInvalidValue;
       return launch_rows_e<EPI_QKV>(tile, p, s, e0, e1);
     default: return hipErrorInvalidValue;
   }
@@ -923,7 +930,7 @@ bool gemm_config_ok(int dtype, int epi, int nt, int mt, int kw, int grid_x, int 
   }
   if (grid_z * 16 * mt < p.M || kbytes % GEMM_CHUNK) return false;
   if (ksplit < 1 || (ksplit > 1 && epi != EPI_PART) || ksplit > (int)(kbytes / GEMM_CHUNK)) return false;
-  if (epi == EPI_QKV && (kw != 4 || p.rope.hd % 16 || p.N != (p.rope.H + 2 * p.rope.KV) * p.rope.hd)) return false;
+  if (epi == EPI_QKV && (kw != 4 || !qkv_shape_ok(p))) return false;
   return true;
 }
 

@@ -443,7 +443,8 @@ int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, i
 
 // One forward pass of a model over the rows set up by `rows` (or already in
 // the lane for prefill).  lm_M > 0: final norm over rows r*lm_stride+lm_off
-// and LM head into `logits` [lm_M, V].
+// and LM head into `logits` [lm_M, V]; lm_M = 0: the pass only extends the KV
+// cache (prefill).
 int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, const int32_t* rowblocks,
             int R, int attn_splits, int qmax, int lm_M, int lm_stride, int lm_off, float* logits,
             const int32_t* bt, bool verify, hipStream_t s) {
@@ -482,8 +483,13 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     rp.KV = c.n_kv_heads;
     rp.hd = c.head_dim;
     rp.nblk = m.n_blocks;
-    int rc = gemm(ctx, m, EPI_QKV, ln.xn, m.wqkv[l], M, m.nqkv(), d, nullptr, 0, nullptr, s, pk_all, -1, &rp);
-    if (rc) return rc;
+    // without a head nothing reads the last layer's output: its rows only add
+    // their keys and values to the cache (the last 2 KV hd rows of wqkv)
+    const bool kv_only = lm_M == 0 && l + 1 == c.n_layers;
+    rp.col0 = kv_only ? m.nq() : 0;
+    const void* wqkv = (const unsigned char*)m.wqkv[l] + (size_t)rp.col0 * d * m.esz;
+    int rc = gemm(ctx, m, EPI_QKV, ln.xn, wqkv, M, m.nqkv() - rp.col0, d, nullptr, 0, nullptr, s, pk_all, -1, &rp);
+    if (rc || kv_only) return rc;
     AttnParams ap{};
     ap.q = ln.q;
     ap.kv = rp.kv;
@@ -536,9 +542,8 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     rc = gemm(ctx, m, EPI_SWIGLU, ln.xn, m.wgu[l], M, 2 * c.d_ffn, d, nullptr, 0, ln.hmid, s, pk_all,
               verify ? SD_PROF_GEMM_VERIFY_GATEUP : -1);
     if (rc) return rc;
-    const bool norm_next = l + 1 < c.n_layers || lm_M > 0;
     rc = gemm(ctx, m, EPI_RESID, ln.hmid, m.wdown[l], M, d, c.d_ffn, ln.x, d, nullptr, s, pk_all, -1, nullptr,
-              ln.part, norm_next ? max_split : 1, &ns);
+              ln.part, max_split, &ns);
     if (rc) return rc;
     if (l + 1 < c.n_layers) {
       NormParams nn{ln.x, ns ? ln.part : nullptr, ns, m.attn_norm[l + 1], ln.xn, M, d, 1, 0, M, c.rms_eps};

@@ -153,6 +153,7 @@ struct RopeParams {
   const int32_t* row_pos;      // [M]; -1 = inactive row
   const int32_t* row_blk;      // [M] KV block of the row's position; -1 = not written
   int H, KV, hd, nblk;         // nblk: blocks in the pool
+  int col0;                    // first column of the fused projection that is computed (0, or H hd: keys and values only)
 };
 
 struct GemmParams {
