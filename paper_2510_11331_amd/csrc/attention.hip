@@ -355,10 +355,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   // unit 64 s, this lane's 16 bytes at unit 64 s + lane (token r16, dims
   // g HD/4 + 8 s .. + 8); the V tile follows the K tile of the same block
   const uint32_t koff = (uint32_t)lane * 16u;
-  // V tile (kv_val_off): unit 4 r16 + g of 32-dim group dp holds tokens
+  // V tile (kv_val_off): unit 16 g + r16 of 32-dim group dp holds tokens
   // 4g..4g+3 of dims 32 dp + r16 and 32 dp + 16 + r16 (the 64 lanes read the
   // group's 1 KB)
-  const uint32_t voff = 16u * HD * 2u + (uint32_t)(4 * r16 + g) * 16u;
+  const uint32_t voff = 16u * HD * 2u + (uint32_t)lane * 16u;
 
   // two register stages of one 32-key step: K rows (two blocks), V^T quads
   // as loaded, and the masks of the V entries past the key range (applied

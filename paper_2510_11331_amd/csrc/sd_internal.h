@@ -62,12 +62,15 @@ template <typename T> __host__ __device__ __forceinline__ int kv_key_off(int t, 
 
 // Element offset of value (token t, dim d) inside one 16-token V tile.  bf16
 // caches: for each 32-dim group the 16 x 32 slice is ordered
-// [dim % 16][t / 4][(d / 16) % 2][t % 4], so that the 4 consecutive tokens of
-// two dims 16 apart are one 16-byte unit and a wave load of 64 such units is
-// one contiguous 1 KB.  fp32 caches: transposed, [hd][16].
+// [t / 4][dim % 16][(d / 16) % 2][t % 4], so that the 4 consecutive tokens of
+// two dims 16 apart are one 16-byte unit, a wave load of 64 such units is
+// one contiguous 1 KB, and the units of a token quad are 256 contiguous bytes:
+// a decode pass that appends a few tokens writes whole or half memory lines
+// instead of a few bytes of every line of the tile.  fp32 caches: transposed,
+// [hd][16].
 template <typename T> __host__ __device__ __forceinline__ int kv_val_off(int t, int d, int hd) {
   if constexpr (sizeof(T) == 2) {
-    return ((((d >> 5) * 16 + (d & 15)) * 4 + (t >> 2)) * 2 + ((d >> 4) & 1)) * 4 + (t & 3);
+    return ((((d >> 5) * 4 + (t >> 2)) * 16 + (d & 15)) * 2 + ((d >> 4) & 1)) * 4 + (t & 3);
   } else {
     return d * 16 + t;
   }

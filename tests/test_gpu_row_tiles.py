@@ -72,19 +72,25 @@ def test_prefill_chunk_matches_oracle(shape, rows):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7)])
+@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7), (70, 1)])
 def test_batched_verify_matches_oracle(B, gamma):
-    """65, 120 and 264 verified rows: K-split residual projections and an LM head whose last column tile is partial."""
+    """65 to 264 verified rows: K-split residual projections, an LM head whose last column tile is partial, values of
+    several tasks in one row tile (and, in the 140 rows of the last case's first draft call, every other row inactive)."""
     say("row tiles, verify", B, gamma)
     prompts = synth.prompts(B, [5 + k % 7 for k in range(B)], NARROW.vocab)
     tw, dw = synth.model_weights(NARROW, 5), synth.model_weights(DRAFT, 6)
     eng = make_engine(NARROW, DRAFT, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
     _, _, b, z = run_gpu_steps(eng, list(range(B)), prompts, gamma, 1, 9, list(range(B)), keep_logits=True)
-    drafts = b.draft_tok.cpu().numpy()
+    drafts, q = b.draft_tok.cpu().numpy(), b.q.cpu().numpy().astype(np.float64)
     assert eng.check_flags() == 0
     eng.close()
-    ref = om.Model(NARROW, tw).sequence_logits([list(p) + [int(t) for t in drafts[k]] for k, p in enumerate(prompts)],
-                                               gamma + 1)
+    seqs = [list(p) + [int(t) for t in drafts[k]] for k, p in enumerate(prompts)]
+    ref = om.Model(NARROW, tw).sequence_logits(seqs, gamma + 1)
+    zd = om.Model(DRAFT, dw).sequence_logits([sq[:-1] for sq in seqs], gamma)
+    for k in range(B):
+        for i in range(gamma):
+            dlog = np.log(q[k, i]) - zd[k][i]
+            assert np.ptp(dlog) < 2 * BOUND * np.abs(zd[k][i]).max(), (k, i)
     for k in range(B):
         for j in range(gamma + 1):
             err = float(np.abs(z[0, k, j] - ref[k][j]).max() / np.abs(ref[k][j]).max())
