@@ -257,17 +257,27 @@ __device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c) {
                                                 0, 0);
 }
 
-// Wave w of a workgroup (WAVES = 8) takes query tile w % QTe (16 query
-// vectors) and key group w / QTe: 32-key steps kb = k_begin + 32 (kg + KG j).
-// Lane (r16, g): query r16 of the tile; in S^T it holds keys 4g..4g+3 of
+// A workgroup's query tiles (16 query vectors each, QT of them) are taken
+// `per` to a wave: wave w takes tiles (w % QG) per .. + per - 1 and key group
+// w / QG, the 32-key steps kb = k_begin + 32 (kg + KG j).  per is 1 for short
+// key ranges: the QT waves of a key group then load the same keys.  From
+// QPW_KEYS keys on it is QPW (> 1 for hd 64 with 2 or 3 tiles): each key tile
+// is loaded once for all of them, so the loads in flight that hide the memory
+// latency are of QT times as many keys (small target, two tasks at 15500
+// keys, gamma = 8, four layers: verify pass 338 -> 321 us), but more key groups
+// are merged at the end (the same target at 520 keys, 16 layers: step 1271 ->
+// 1301 us, hence the limit).
+// Lane (r16, g): query r16 of a tile; in S^T it holds keys 4g..4g+3 of
 // both blocks of the step, in O^T dimensions 16 dt + 4g .. +3.
-template <int HD, int WAVES>
+constexpr int QPW_KEYS = 512;            // 8 key groups of two 32-key steps
+
+template <int HD, int WAVES, int QPW>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(AttnParams p) {
   constexpr int UPG = HD / 32;             // 16-byte K units per lane group (HD/4 dims)
   constexpr int DT = HD / 16;              // 16-dimension output tiles
   constexpr int NSLOT = WAVES / 2;         // merge slots: half the waves hand over in the first round
-  __shared__ float s_o[NSLOT][16][HD + 4];
-  __shared__ float s_m[NSLOT][16], s_l[NSLOT][16];
+  __shared__ float s_o[NSLOT * QPW][16][HD + 4];
+  __shared__ float s_m[NSLOT * QPW][16], s_l[NSLOT * QPW][16];
 
   __shared__ int s_bt[ATTN_BT_CAP];
 
@@ -288,11 +298,6 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   const int G = p.H / p.KV;
   const int Qn = nr * G;
   const int QT = (Qn + 15) >> 4;
-  const int QTe = QT == 3 ? 4 : QT;
-  const int KG = WAVES / QTe;
-  const int qt = wave % QTe, kg = wave / QTe;
-  const bool wave_on = qt < QT;
-
   // the block's rows (nr <= 64: Qn is at most 64 query vectors) in parallel
   int maxpos = lane < nr ? p.row_pos[row0 + lane] : -1;
 #pragma unroll
@@ -307,6 +312,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   const int k_begin = split * kps;
   const int k_end = min(min(k_begin + kps, maxpos + 1), p.mbps * 16);
 
+  const int per = QPW > 1 && k_end - k_begin >= QPW_KEYS ? QPW : 1;
+  const int QGn = (QT + per - 1) / per;    // wave groups (1 .. 4; 3 take the waves of 4)
+  const int QG = QGn == 3 ? 4 : QGn;
+  const int KG = WAVES / QG;
+  const int qg = wave % QG, kg = wave / QG;
+  const bool wave_on = qg < QGn;
+
   // block ids of the split's key range, staged in LDS (the host keeps a
   // split within ATTN_BT_CAP blocks): a key load then never waits on the
   // memory counter behind the keys still in flight
@@ -315,16 +327,18 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   for (int i = tid; i < min(nbr, ATTN_BT_CAP); i += blockDim.x) s_bt[i] = bt[bfirst + i];
   __syncthreads();
 
-  const int qi = qt * 16 + r16;
-  const bool qvalid = wave_on && qi < Qn;
-  const int qrow = row0 + (qvalid ? qi / G : 0);
-  const int qh = kvh * G + (qvalid ? qi % G : 0);
-  const int qpos = qvalid ? p.row_pos[qrow] : -1;
-
-  u32x4 qhi[UPG], qlo[UPG];
-  {
+  int qi[QPW], qrow[QPW], qh[QPW], qpos[QPW];
+  bool qvalid[QPW];
+  u32x4 qhi[QPW][UPG], qlo[QPW][UPG];
+#pragma unroll
+  for (int t = 0; t < QPW; ++t) {
+    qi[t] = (qg * per + t) * 16 + r16;
+    qvalid[t] = wave_on && t < per && qi[t] < Qn;
+    qrow[t] = row0 + (qvalid[t] ? qi[t] / G : 0);
+    qh[t] = kvh * G + (qvalid[t] ? qi[t] % G : 0);
+    qpos[t] = qvalid[t] ? p.row_pos[qrow[t]] : -1;
     // always-valid address (row0, head kvh G for idle lanes), zeroed after the load
-    const float4* qs = (const float4*)(p.q + (size_t)qrow * p.H * HD + (size_t)qh * HD + g * (HD / 4));
+    const float4* qs = (const float4*)(p.q + (size_t)qrow[t] * p.H * HD + (size_t)qh[t] * HD + g * (HD / 4));
     float4 xv[2 * UPG];
 #pragma unroll
     for (int s = 0; s < 2 * UPG; ++s) xv[s] = qs[s];
@@ -332,17 +346,22 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
     for (int s = 0; s < UPG; ++s) {
       // scores in log2 units (q pre-scaled by log2 e): the softmax then
       // uses the hardware base-2 exponential
-      const float sc = qvalid ? p.scale * 1.4426950408889634f : 0.f;
+      const float sc = qvalid[t] ? p.scale * 1.4426950408889634f : 0.f;
       float x[8] = {xv[2 * s].x * sc, xv[2 * s].y * sc, xv[2 * s].z * sc, xv[2 * s].w * sc,
                     xv[2 * s + 1].x * sc, xv[2 * s + 1].y * sc, xv[2 * s + 1].z * sc, xv[2 * s + 1].w * sc};
-      split8(x, qhi[s], qlo[s]);
+      split8(x, qhi[t][s], qlo[t][s]);
     }
   }
 
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o[DT];
+  float m_run[QPW], l_run[QPW];
+  f32x4 o[QPW][DT];
 #pragma unroll
-  for (int d = 0; d < DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < QPW; ++t) {
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+#pragma unroll
+    for (int d = 0; d < DT; ++d) o[t][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   // this kv head's region of the pool ([blocks][K|V][16 x HD], 2 x 16 HD
   // fp16 per block) as a range-checked buffer: steps past the key range
@@ -388,57 +407,61 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
     __builtin_amdgcn_sched_barrier(0);
   };
   auto step = [&]<int S>(int kb) {
-    // four independent accumulation chains (the hi and lo parts of q for
-    // each of the two key blocks), so that consecutive matrix instructions
-    // do not wait on each other's results; the parts are added at the end
-    f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0, s0l = s0, s1l = s0;
 #pragma unroll
-    for (int s = 0; s < UPG; ++s) {
-      s0 = mfma_f16(Kf[S][0][s], qhi[s], s0);
-      s1 = mfma_f16(Kf[S][1][s], qhi[s], s1);
-      s0l = mfma_f16(Kf[S][0][s], qlo[s], s0l);
-      s1l = mfma_f16(Kf[S][1][s], qlo[s], s1l);
-    }
-    s0 += s0l;
-    s1 += s1l;
-    float sc[8];
-    bool ok[8];
+    for (int t = 0; t < QPW; ++t) {
+      if (t >= per) continue;
+      // four independent accumulation chains (the hi and lo parts of q for
+      // each of the two key blocks), so that consecutive matrix instructions
+      // do not wait on each other's results; the parts are added at the end
+      f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0, s0l = s0, s1l = s0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int k0 = kb + 4 * g + v, k1 = k0 + 16;
-      ok[v] = k0 < k_end && k0 <= qpos;
-      ok[4 + v] = k1 < k_end && k1 <= qpos;
-      sc[v] = s0[v];
-      sc[4 + v] = s1[v];
-    }
-    float mx = -INFINITY;
+      for (int s = 0; s < UPG; ++s) {
+        s0 = mfma_f16(Kf[S][0][s], qhi[t][s], s0);
+        s1 = mfma_f16(Kf[S][1][s], qhi[t][s], s1);
+        s0l = mfma_f16(Kf[S][0][s], qlo[t][s], s0l);
+        s1l = mfma_f16(Kf[S][1][s], qlo[t][s], s1l);
+      }
+      s0 += s0l;
+      s1 += s1l;
+      float sc[8];
+      bool ok[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mx = ok[e] ? fmaxf(mx, sc[e]) : mx;
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mnew = fmaxf(m_run, mx);
-    float pe[8], sum = 0.f;
+      for (int v = 0; v < 4; ++v) {
+        const int k0 = kb + 4 * g + v, k1 = k0 + 16;
+        ok[v] = k0 < k_end && k0 <= qpos[t];
+        ok[4 + v] = k1 < k_end && k1 <= qpos[t];
+        sc[v] = s0[v];
+        sc[4 + v] = s1[v];
+      }
+      float mx = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pe[e] = ok[e] ? exp2f(sc[e] - mnew) : 0.f;
-      sum += pe[e];
-    }
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
-    const float alpha = m_run == -INFINITY ? 0.f : exp2f(m_run - mnew);
-    l_run = l_run * alpha + sum;
-    m_run = mnew;
-    u32x4 phi, plo;
-    split8(pe, phi, plo);
+      for (int e = 0; e < 8; ++e) mx = ok[e] ? fmaxf(mx, sc[e]) : mx;
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mnew = fmaxf(m_run[t], mx);
+      float pe[8], sum = 0.f;
 #pragma unroll
-    for (int d = 0; d < DT; ++d) {
-      o[d] *= alpha;
-      // dims d (even d: x, y of the unit) of tokens 4g..4g+3 of both blocks
-      const u32x4 v0 = Vr[S][0][d / 2], v1 = Vr[S][1][d / 2];
-      const u32x4 va = (d & 1) ? u32x4{v0.z & Vm[S][0][0], v0.w & Vm[S][0][1], v1.z & Vm[S][1][0], v1.w & Vm[S][1][1]}
-                               : u32x4{v0.x & Vm[S][0][0], v0.y & Vm[S][0][1], v1.x & Vm[S][1][0], v1.y & Vm[S][1][1]};
-      o[d] = mfma_f16(va, phi, o[d]);
-      o[d] = mfma_f16(va, plo, o[d]);
+      for (int e = 0; e < 8; ++e) {
+        pe[e] = ok[e] ? exp2f(sc[e] - mnew) : 0.f;
+        sum += pe[e];
+      }
+      sum += __shfl_xor(sum, 16);
+      sum += __shfl_xor(sum, 32);
+      const float alpha = m_run[t] == -INFINITY ? 0.f : exp2f(m_run[t] - mnew);
+      l_run[t] = l_run[t] * alpha + sum;
+      m_run[t] = mnew;
+      u32x4 phi, plo;
+      split8(pe, phi, plo);
+#pragma unroll
+      for (int d = 0; d < DT; ++d) {
+        o[t][d] *= alpha;
+        // dims d (even d: x, y of the unit) of tokens 4g..4g+3 of both blocks
+        const u32x4 v0 = Vr[S][0][d / 2], v1 = Vr[S][1][d / 2];
+        const u32x4 va = (d & 1) ? u32x4{v0.z & Vm[S][0][0], v0.w & Vm[S][0][1], v1.z & Vm[S][1][0], v1.w & Vm[S][1][1]}
+                                 : u32x4{v0.x & Vm[S][0][0], v0.y & Vm[S][0][1], v1.x & Vm[S][1][0], v1.y & Vm[S][1][1]};
+        o[t][d] = mfma_f16(va, phi, o[t][d]);
+        o[t][d] = mfma_f16(va, plo, o[t][d]);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -461,72 +484,92 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
 
   // merge the key groups of each query tile into key group 0 as a binary
   // tree (fixed order): in the round of stride h, key group kg with
-  // kg % 2h == h hands its state to kg - h through slot qt KG/2 + kg / 2h
+  // kg % 2h == h hands its state to kg - h through slot qg KG/2 + kg / 2h
   for (int h = 1; h < KG; h *= 2) {
-    const int sl = qt * (KG / 2) + kg / (2 * h);
+    const int sl = (qg * (KG / 2) + kg / (2 * h)) * QPW;
     if (wave_on && kg % (2 * h) == h) {
-      if (g == 0) {
-        s_m[sl][r16] = m_run;
-        s_l[sl][r16] = l_run;
+#pragma unroll
+      for (int t = 0; t < QPW; ++t) {
+        if (t >= per) continue;
+        if (g == 0) {
+          s_m[sl + t][r16] = m_run[t];
+          s_l[sl + t][r16] = l_run[t];
+        }
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) s_o[sl + t][r16][16 * d + 4 * g + v] = o[t][d][v];
       }
-#pragma unroll
-      for (int d = 0; d < DT; ++d)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s_o[sl][r16][16 * d + 4 * g + v] = o[d][v];
     }
     __syncthreads();
     if (wave_on && kg % (2 * h) == 0) {
-      const float mb = s_m[sl][r16], lb = s_l[sl][r16];
-      const float M = fmaxf(m_run, mb);
-      const float a = m_run == -INFINITY ? 0.f : exp2f(m_run - M);
-      const float b = mb == -INFINITY ? 0.f : exp2f(mb - M);
-      l_run = l_run * a + lb * b;
 #pragma unroll
-      for (int d = 0; d < DT; ++d)
+      for (int t = 0; t < QPW; ++t) {
+        if (t >= per) continue;
+        const float mb = s_m[sl + t][r16], lb = s_l[sl + t][r16];
+        const float M = fmaxf(m_run[t], mb);
+        const float a = m_run[t] == -INFINITY ? 0.f : exp2f(m_run[t] - M);
+        const float b = mb == -INFINITY ? 0.f : exp2f(mb - M);
+        l_run[t] = l_run[t] * a + lb * b;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[d][v] = o[d][v] * a + s_o[sl][r16][16 * d + 4 * g + v] * b;
-      m_run = M;
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) o[t][d][v] = o[t][d][v] * a + s_o[sl + t][r16][16 * d + 4 * g + v] * b;
+        m_run[t] = M;
+      }
     }
     __syncthreads();
   }
-  const bool owner = wave_on && kg == 0 && qvalid;
-  // four consecutive output dimensions of this lane's query, MFMA-tile layout
-  auto emit4 = [&](int d, float a0, float a1, float a2, float a3) {
-    const size_t off = Tile<f16_t>::off(qrow, qh * HD + 16 * d + 4 * g, p.H * HD);
-    *(uint2*)((f16_t*)p.out + off) = make_uint2((uint32_t)f2h(a0) | ((uint32_t)f2h(a1) << 16),
-                                                (uint32_t)f2h(a2) | ((uint32_t)f2h(a3) << 16));
-  };
+  const bool first = wave_on && kg == 0;     // holds the merged state of its tiles
 
   if (p.splits == 1) {
-    if (owner) {
-      const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+    if (first) {
 #pragma unroll
-      for (int d = 0; d < DT; ++d) emit4(d, o[d][0] * inv, o[d][1] * inv, o[d][2] * inv, o[d][3] * inv);
+      for (int t = 0; t < QPW; ++t) {
+        if (!qvalid[t]) continue;
+        const float inv = l_run[t] > 0.f ? 1.0f / l_run[t] : 0.f;
+        // four consecutive output dimensions of this lane's query, MFMA-tile layout
+#pragma unroll
+        for (int d = 0; d < DT; ++d) {
+          const size_t off = Tile<f16_t>::off(qrow[t], qh[t] * HD + 16 * d + 4 * g, p.H * HD);
+          *(uint2*)((f16_t*)p.out + off) =
+              make_uint2((uint32_t)f2h(o[t][d][0] * inv) | ((uint32_t)f2h(o[t][d][1] * inv) << 16),
+                         (uint32_t)f2h(o[t][d][2] * inv) | ((uint32_t)f2h(o[t][d][3] * inv) << 16));
+        }
+      }
     }
     return;
   }
 
   // key split: this workgroup's partial (output, max, sum) goes out with
   // device-scope stores; the item's last split to finish merges them.  Every
-  // value handed over is written and read with device-scope atomic
-  // operations, which the L2 of another XCD does not serve stale, so waiting
-  // for the stores before counting is all the ordering needed (a release /
-  // acquire fence would also write back and invalidate the whole L2, which
-  // only data written with plain stores needs)
+  // value handed over is written and read with device-scope (sc1) accesses,
+  // which the L2 of another XCD does not serve stale, so waiting for the
+  // stores before counting is all the ordering needed (a release / acquire
+  // fence would also write back and invalidate the whole L2, which only data
+  // written with plain stores needs).  16 bytes at a time: the hand-over and
+  // the merge are a chain of memory round trips, and 4-byte accesses made
+  // several rounds of each (verify pass of two 7B layers at B = 1 255 -> 250 us,
+  // of the small target's 16 at B = 8 with its drafts 1321 -> 1271)
+  constexpr int SC1 = 16;
   const size_t base = (size_t)rbk * p.splits * p.qmax;
-  const size_t item = base + (size_t)split * p.qmax + (owner ? qi : 0);
-  if (owner) {
+  const uint32_t nvec = (uint32_t)p.splits * p.qmax;
+  const __amdgpu_buffer_rsrc_t por =
+      __builtin_amdgcn_make_buffer_rsrc(p.part_o + base * HD, (short)0, (int)(nvec * HD * 4u), 0x00020000);
+  const __amdgpu_buffer_rsrc_t pmr =
+      __builtin_amdgcn_make_buffer_rsrc(p.part_ml + base * 2, (short)0, (int)(nvec * 8u), 0x00020000);
+  if (first) {
 #pragma unroll
-    for (int d = 0; d < DT; ++d)
+    for (int t = 0; t < QPW; ++t) {
+      if (!qvalid[t]) continue;
+      const uint32_t item = (uint32_t)(split * p.qmax + qi[t]);
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        __hip_atomic_store(p.part_o + item * HD + 16 * d + 4 * g + v, o[d][v], __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    if (g == 0) {
-      // natural units for the merge
-      __hip_atomic_store(p.part_ml + item * 2, m_run == -INFINITY ? -INFINITY : m_run * 0.6931471805599453f,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(p.part_ml + item * 2 + 1, l_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int d = 0; d < DT; ++d)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[t][d]), por,
+                                               (item * HD + 16u * d + 4u * g) * 4u, 0, SC1);
+      if (g == 0)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(m_run[t]), __float_as_uint(l_run[t])}, pmr,
+                                              item * 8u, 0, SC1);
     }
   }
   __shared__ int s_last;
@@ -541,46 +584,41 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   __syncthreads();
   if (!s_last) return;
 
-  // merge, in split order: O = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M),
-  // M = max_s m_s; every load of a query's splits is issued before any is used
-  __shared__ float s_w[ATTN_QMAX][ATTN_MAX_SPLITS], s_L[ATTN_QMAX];
-  for (int qj = tid; qj < Qn; qj += 64 * WAVES) {
-    float ms[ATTN_MAX_SPLITS], ls[ATTN_MAX_SPLITS];
+  // merge, in split order: O = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M),
+  // M = max_s m_s (log2 units); every load of four output dimensions of a
+  // query (all splits' max, sum and output) is issued before any is used
+  for (int idx = tid; idx < Qn * (HD / 4); idx += 64 * WAVES) {
+    const int qj = idx / (HD / 4), c = idx % (HD / 4);
+    u32x2 ml[ATTN_MAX_SPLITS];
+    u32x4 os[ATTN_MAX_SPLITS];
 #pragma unroll
     for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) {
-      const size_t it = (base + (size_t)sp * p.qmax + qj) * 2;
-      ms[sp] = sp < p.splits ? __hip_atomic_load(p.part_ml + it, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                             : -INFINITY;
-      ls[sp] = sp < p.splits ? __hip_atomic_load(p.part_ml + it + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                             : 0.f;
+      // splits past the last read nothing (out-of-range offset: zeros)
+      const uint32_t it = (uint32_t)(sp * p.qmax + qj);
+      ml[sp] = __builtin_bit_cast(
+          u32x2, __builtin_amdgcn_raw_buffer_load_b64(pmr, sp < p.splits ? it * 8u : 0x80000000u, 0, SC1));
+      os[sp] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(por, sp < p.splits ? (it * HD + 4u * c) * 4u : 0x80000000u, 0, SC1));
     }
     float M = -INFINITY;
 #pragma unroll
-    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) M = fmaxf(M, ms[sp]);
+    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp)
+      if (sp < p.splits) M = fmaxf(M, __uint_as_float(ml[sp].x));
     float L = 0.f;
+    float O[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) {
-      const float w = ms[sp] == -INFINITY ? 0.f : expf(ms[sp] - M);
-      L += ls[sp] * w;
-      s_w[qj][sp] = w;
+      const float ms = __uint_as_float(ml[sp].x);
+      const float w = sp < p.splits && ms != -INFINITY ? exp2f(ms - M) : 0.f;
+      L += __uint_as_float(ml[sp].y) * w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) O[e] += __uint_as_float(os[sp][e]) * w;
     }
-    s_L[qj] = L;
-  }
-  __syncthreads();
-  for (int idx = tid; idx < Qn * HD; idx += 64 * WAVES) {
-    const int qj = idx / HD, d = idx % HD;
-    float os[ATTN_MAX_SPLITS];
-#pragma unroll
-    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp)
-      os[sp] = sp < p.splits ? __hip_atomic_load(p.part_o + (base + (size_t)sp * p.qmax + qj) * HD + d,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                             : 0.f;
-    float O = 0.f;
-#pragma unroll
-    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) O += os[sp] * s_w[qj][sp];
-    const float L = s_L[qj];
     const int row = row0 + qj / G, h = kvh * G + qj % G;
-    Store<f16_t>::store((f16_t*)p.out, Tile<f16_t>::off(row, h * HD + d, p.H * HD), L > 0.f ? O / L : 0.f);
+    const float inv = L > 0.f ? 1.0f / L : 0.f;
+    *(uint2*)((f16_t*)p.out + Tile<f16_t>::off(row, h * HD + 4 * c, p.H * HD)) =
+        make_uint2((uint32_t)f2h(O[0] * inv) | ((uint32_t)f2h(O[1] * inv) << 16),
+                   (uint32_t)f2h(O[2] * inv) | ((uint32_t)f2h(O[3] * inv) << 16));
   }
 }
 
@@ -665,15 +703,28 @@ hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t s, hipEv
     // a two-round key-group merge instead of three, 14.2 -> 13.9 us per
     // layer (with twice the splits on them, 14.8)
     const bool many = grid.x * grid.y >= (p.hd == 64 ? 1024u : 2048u) || (p.hd == 128 && p.splits > 1);
+    // hd 64, more than one query tile (grouped KV heads, long speculation): up
+    // to three tiles in one wave where its key range is long (QPW_KEYS).  hd 128
+    // has no registers for a second tile
+    const int qt = (p.qmax + 15) / 16, qpw = p.hd == 64 && qt > 1 ? (qt == 3 ? 3 : 2) : 1;
+#define SD_ATTN(HDv, Wv, Qv) launch_k(attention_mfma_kernel<HDv, Wv, Qv>, grid, dim3(64 * Wv), 0, s, e0, e1, p)
     if (p.hd == 64) {
-      if (many) launch_k(attention_mfma_kernel<64, 4>, grid, dim3(64 * 4), 0, s, e0, e1, p);
-      else launch_k(attention_mfma_kernel<64, 8>, grid, dim3(64 * 8), 0, s, e0, e1, p);
+      if (many) {
+        if (qpw == 1) SD_ATTN(64, 4, 1);
+        else if (qpw == 2) SD_ATTN(64, 4, 2);
+        else SD_ATTN(64, 4, 3);
+      } else {
+        if (qpw == 1) SD_ATTN(64, 8, 1);
+        else if (qpw == 2) SD_ATTN(64, 8, 2);
+        else SD_ATTN(64, 8, 3);
+      }
     } else if (p.hd == 128) {
-      if (many) launch_k(attention_mfma_kernel<128, 4>, grid, dim3(64 * 4), 0, s, e0, e1, p);
-      else launch_k(attention_mfma_kernel<128, 8>, grid, dim3(64 * 8), 0, s, e0, e1, p);
+      if (many) SD_ATTN(128, 4, 1);
+      else SD_ATTN(128, 8, 1);
     } else {
       return hipErrorInvalidValue;
     }
+#undef SD_ATTN
     return hipGetLastError();
   }
   if (p.hd == 64) return launch_attn_t<float, 64>(p, s, e0, e1);
