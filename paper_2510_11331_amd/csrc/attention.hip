@@ -25,12 +25,12 @@
 // kernel leaves the merge to a second kernel).
 //
 // bf16 models (fp16 KV cache, see f16_t): S^T = K Q^T and O^T += V^T P^T on
-// v_mfma_f32_16x16x32_f16, 16 query vectors per wave, keys streamed from the
-// cache straight into registers 32 at a time (two blocks), one step ahead,
-// with non-temporal loads (each cache byte is read once per pass); q and p
-// enter the matrix instruction as fp16 hi + lo pairs, which keeps them at
-// ~2^-22 relative precision.  fp32 models: a vector kernel with K/V staged
-// in LDS.
+// v_mfma_f32_16x16x32_f16; q and p enter the matrix instruction as fp16 hi + lo
+// pairs, which keeps them at ~2^-22 relative precision.  Decode passes stream
+// the keys from the cache straight into registers 32 at a time (two blocks),
+// one step ahead, with non-temporal loads (each cache byte is read once per
+// pass); prefill passes share K/V tiles in LDS between eight waves of 16 query
+// vectors.  fp32 models: a vector kernel with K/V staged in LDS.
 #include "sd_internal.h"
 
 #include <algorithm>
@@ -287,14 +287,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   const int rbk = blockIdx.x;
   const int rb = rbk / p.KV, kvh = rbk % p.KV;
   const int split = blockIdx.y;
-  int row0, nr;
-  if (p.rowblocks) {
-    row0 = p.rowblocks[2 * rb];
-    nr = p.rowblocks[2 * rb + 1];
-  } else {
-    row0 = rb * p.R;
-    nr = p.R;
-  }
+  const int row0 = rb * p.R, nr = p.R;
   const int G = p.H / p.KV;
   const int Qn = nr * G;
   const int QT = (Qn + 15) >> 4;
@@ -303,7 +296,6 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) maxpos = max(maxpos, __shfl_xor(maxpos, o));
   maxpos = __builtin_amdgcn_readfirstlane(maxpos);
-  const int slot = p.row_bt ? 0 : p.row_slot[row0];   // decode passes: the row block's own table row
   // the item's keys (positions 0 .. maxpos) are dealt out evenly over the
   // splits in 32-key steps, at most the host's keys_per_split per split
   // (which bounds the staged block ids)
@@ -322,7 +314,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   // block ids of the split's key range, staged in LDS (the host keeps a
   // split within ATTN_BT_CAP blocks): a key load then never waits on the
   // memory counter behind the keys still in flight
-  const int32_t* bt = (p.row_bt ? p.row_bt + (size_t)rb * p.mbps : p.block_table + (size_t)slot * p.mbps);
+  const int32_t* bt = p.row_bt + (size_t)rb * p.mbps;   // the row block's own table row
   const int bfirst = k_begin / 16, nbr = max(0, (k_end + 15) / 16 - bfirst);
   for (int i = tid; i < min(nbr, ATTN_BT_CAP); i += blockDim.x) s_bt[i] = bt[bfirst + i];
   __syncthreads();
@@ -622,6 +614,200 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
   }
 }
 
+// Prefill attention of 16-bit caches: up to ATTN_PREFILL_Q query vectors (a
+// run of rows of one task, all query heads of one kv head) per workgroup of
+// eight waves, one tile of 16 per wave.  Here every key meets more than a
+// hundred queries, so the matrix instructions bound the kernel and not the
+// cache stream: the K/V tiles are loaded into LDS once per workgroup (64 keys a
+// stage, half a block per wave, two stages) and each operand a wave reads from
+// there feeds both fp16 parts of q or p.  What is left beside them is the
+// softmax, kept small: no masks on steps all of a wave's queries see, row sums
+// left per lane until the end, and the running maximum only raised (with its
+// lane exchanges and the rescaling of the output) when a score passes it by
+// more than 8 in log2 units, so p stays within 2^8 and every step in between
+// is exact relative to the same reference.  Row blocks run last to first: the
+// ones with the most keys start first.
+// Measured per layer (the decode kernel, which streams the keys into each
+// wave's registers, before): 7B, a 2048-row chunk of ragged prompts 178 -> 80
+// us, one prompt of 1024 tokens 64 -> 39; the small target's last chunk of
+// 15000 tokens 1024 -> 310.  Four waves with two tiles each (half the LDS
+// reads per matrix instruction): 87, 46 and 351 us.
+constexpr int PF_KEYS = 64;
+
+template <int HD>
+__global__ __launch_bounds__(512, 2) void attention_prefill_kernel(AttnParams p) {
+  constexpr int UPG = HD / 32, DT = HD / 16, WAVES = ATTN_PREFILL_Q / 16;
+  constexpr uint32_t BLK_BYTES = 2u * 16u * HD * 2u;   // K and V tile of a block
+  constexpr int WPB = WAVES * 16 / PF_KEYS;            // waves that load a block of a stage
+  constexpr int NL = (int)BLK_BYTES / 1024 / WPB;      // loads of a wave per stage
+  constexpr int UNITS = (int)BLK_BYTES / 16;           // 16-byte units of a block
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  u32x4* lds = (u32x4*)smem;                           // [2][PF_KEYS / 16][UNITS]
+  __shared__ int s_bt[ATTN_BT_CAP];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int rb = p.nrb - 1 - (int)blockIdx.x / p.KV, kvh = blockIdx.x % p.KV;
+  const int row0 = p.rowblocks[2 * rb], nr = p.rowblocks[2 * rb + 1];
+  const int G = p.H / p.KV;
+  const int Qn = nr * G;
+
+  int maxpos = lane < nr ? p.row_pos[row0 + lane] : -1;
+  if (lane + 64 < nr) maxpos = max(maxpos, p.row_pos[row0 + lane + 64]);   // nr <= ATTN_PREFILL_Q
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) maxpos = max(maxpos, __shfl_xor(maxpos, o));
+  maxpos = __builtin_amdgcn_readfirstlane(maxpos);
+  const int k_end = min(maxpos + 1, p.mbps * 16);
+  const int stages = (k_end + PF_KEYS - 1) / PF_KEYS;
+  const int32_t* bt = p.block_table + (size_t)p.row_slot[row0] * p.mbps;
+  for (int i = tid; i < min((k_end + 15) / 16, ATTN_BT_CAP); i += 64 * WAVES) s_bt[i] = bt[i];
+  __syncthreads();
+
+  const int qi = wave * 16 + r16;
+  const bool qvalid = qi < Qn;
+  const int qrow = row0 + (qvalid ? qi / G : 0), qh = kvh * G + (qvalid ? qi % G : 0);
+  const int qpos = qvalid ? p.row_pos[qrow] : -1;
+  u32x4 qhi[UPG], qlo[UPG];
+  {
+    const float4* qs = (const float4*)(p.q + (size_t)qrow * p.H * HD + (size_t)qh * HD + g * (HD / 4));
+    float4 xv[2 * UPG];
+#pragma unroll
+    for (int s = 0; s < 2 * UPG; ++s) xv[s] = qs[s];
+    const float sc = qvalid ? p.scale * 1.4426950408889634f : 0.f;   // scores in log2 units
+#pragma unroll
+    for (int s = 0; s < UPG; ++s) {
+      float x[8] = {xv[2 * s].x * sc, xv[2 * s].y * sc, xv[2 * s].z * sc, xv[2 * s].w * sc,
+                    xv[2 * s + 1].x * sc, xv[2 * s + 1].y * sc, xv[2 * s + 1].z * sc, xv[2 * s + 1].w * sc};
+      split8(x, qhi[s], qlo[s]);
+    }
+  }
+  float m_run = -1e30f, l_lane = 0.f;
+  f32x4 o[DT];
+#pragma unroll
+  for (int d = 0; d < DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // positions of the wave's queries: past wmax there is nothing to see, up to
+  // wmin nothing to mask
+  int wmax = qpos, wmin = qvalid ? qpos : 0x7fffffff;
+#pragma unroll
+  for (int x = 1; x < 16; x <<= 1) {
+    wmax = max(wmax, __shfl_xor(wmax, x));
+    wmin = min(wmin, __shfl_xor(wmin, x));
+  }
+  wmax = __builtin_amdgcn_readfirstlane(wmax);
+  wmin = __builtin_amdgcn_readfirstlane(wmin);
+
+  const __amdgpu_buffer_rsrc_t kvr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<f16_t*>((const f16_t*)p.kv + kv_tile_off(kvh, 0, 0, p.nblk, HD)), (short)0,
+      (int)((uint32_t)p.nblk * BLK_BYTES), 0x00020000);
+  // this wave's share of stage st (part wave % WPB of block wave / WPB) into
+  // its place; blocks past the keys load zeros
+  const int lb = wave / WPB, lc = wave % WPB * NL * 64;
+  auto gload = [&](int st) {
+    const int kt = PF_KEYS * st + 16 * lb;
+    const uint32_t base = kt < k_end ? (uint32_t)s_bt[kt / 16] * BLK_BYTES + (lc + lane) * 16u : 0x80000000u;
+    u32x4* dst = lds + (size_t)((st & 1) * (PF_KEYS / 16) + lb) * UNITS + lc;
+#pragma unroll
+    for (int c = 0; c < NL; ++c) {
+      const uint32_t off = base + 1024u * c;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kvr, (__attribute__((address_space(3))) void*)(dst + 64 * c), 16, off, 0,
+                                               0, 0);
+    }
+  };
+
+  gload(0);
+  for (int st = 0; st < stages; ++st) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt 0: this wave's loads of stage st
+    asm volatile("s_barrier" ::: "memory");            // every block is there; stage st - 1 has been read
+    gload(st + 1);                                     // (past the last stage: zeros)
+    const u32x4* buf = lds + (size_t)(st & 1) * (PF_KEYS / 16) * UNITS;
+    if (st == stages - 1 && (k_end & 15)) {
+      // values past the last key were never written: zero them, so that their
+      // p = 0 never meets a NaN or Inf pattern (their scores are masked)
+      f16_t* vt = (f16_t*)(buf + ((k_end / 16) & 3) * UNITS) + 16 * HD;
+      for (int i = tid; i < 16 * HD; i += 64 * WAVES)
+        if ((i & 15) >= (k_end & 15)) vt[kv_val_off<f16_t>(i & 15, i >> 4, HD)] = (f16_t)0.f;
+      __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt 0
+      asm volatile("s_barrier" ::: "memory");
+    }
+#pragma unroll
+    for (int h = 0; h < PF_KEYS / 32; ++h) {
+      const int kb = PF_KEYS * st + 32 * h;
+      if (kb > wmax) break;
+      const u32x4* b0 = buf + (2 * h) * UNITS + lane;  // the step's two blocks
+      const u32x4* b1 = b0 + UNITS;
+      // four independent chains: the two blocks, the hi and lo part of q
+      f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0, s0l = s0, s1l = s0;
+#pragma unroll
+      for (int s = 0; s < UPG; ++s) {
+        const u32x4 k0 = b0[64 * s], k1 = b1[64 * s];
+        s0 = mfma_f16(k0, qhi[s], s0);
+        s1 = mfma_f16(k1, qhi[s], s1);
+        s0l = mfma_f16(k0, qlo[s], s0l);
+        s1l = mfma_f16(k1, qlo[s], s1l);
+      }
+      s0 += s0l;
+      s1 += s1l;
+      float sc[8];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        sc[v] = s0[v];
+        sc[4 + v] = s1[v];
+      }
+      if (kb + 31 > wmin) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          sc[v] = kb + 4 * g + v <= qpos ? sc[v] : -INFINITY;
+          sc[4 + v] = kb + 16 + 4 * g + v <= qpos ? sc[4 + v] : -INFINITY;
+        }
+      }
+      float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+      if (__any(mx > m_run + 8.0f)) {
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mnew = fmaxf(m_run, mx);
+        const float alpha = exp2f(m_run - mnew);
+        m_run = mnew;
+        l_lane *= alpha;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) o[d] *= alpha;
+      }
+      float pe[8], sum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        pe[e] = __builtin_amdgcn_exp2f(sc[e] - m_run);
+        sum += pe[e];
+      }
+      l_lane += sum;
+      u32x4 phi, plo;
+      split8(pe, phi, plo);
+#pragma unroll
+      for (int dp = 0; dp < DT / 2; ++dp) {
+        const u32x4 v0 = b0[UNITS / 2 + 64 * dp], v1 = b1[UNITS / 2 + 64 * dp];
+        // dims 32 dp + (lane's 4g + v) and + 16 of tokens 4g..4g+3 of both blocks
+        const u32x4 va = u32x4{v0.x, v0.y, v1.x, v1.y}, vb = u32x4{v0.z, v0.w, v1.z, v1.w};
+        o[2 * dp] = mfma_f16(va, phi, o[2 * dp]);
+        o[2 * dp + 1] = mfma_f16(vb, phi, o[2 * dp + 1]);
+        o[2 * dp] = mfma_f16(va, plo, o[2 * dp]);
+        o[2 * dp + 1] = mfma_f16(vb, plo, o[2 * dp + 1]);
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);                  // the loads past the last stage
+
+  float l = l_lane;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (!qvalid) return;
+  const float inv = l > 0.f ? 1.0f / l : 0.f;
+#pragma unroll
+  for (int d = 0; d < DT; ++d) {
+    const size_t off = Tile<f16_t>::off(qrow, qh * HD + 16 * d + 4 * g, p.H * HD);
+    *(uint2*)((f16_t*)p.out + off) = make_uint2((uint32_t)f2h(o[d][0] * inv) | ((uint32_t)f2h(o[d][1] * inv) << 16),
+                                                (uint32_t)f2h(o[d][2] * inv) | ((uint32_t)f2h(o[d][3] * inv) << 16));
+  }
+}
+
 // Merge of the key splits of every (row block, kv head) item of the fp32
 // kernel, in split order: O = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M),
 // M = max_s m_s.  (The matrix kernel merges its splits itself: the last split
@@ -685,12 +871,33 @@ static hipError_t launch_attn_t(const AttnParams& p, hipStream_t s, hipEvent_t e
   return hipGetLastError();
 }
 
+template <int HD>
+static hipError_t launch_prefill(const AttnParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  constexpr int lds = 2 * PF_KEYS * 2 * HD * (int)sizeof(f16_t);
+  static bool attr = false;
+  if (!attr) {
+    hipError_t e = hipFuncSetAttribute((const void*)attention_prefill_kernel<HD>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  launch_k(attention_prefill_kernel<HD>, dim3(p.nrb * p.KV), dim3(512), (uint32_t)lds, s, e0, e1, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (p.nrb <= 0) return hipSuccess;
-  if (p.qmax > ATTN_QMAX) return hipErrorInvalidValue;
   if (p.keys_per_split % 64 || p.keys_per_split > ATTN_BT_CAP * 16) return hipErrorInvalidValue;
   const dim3 grid(p.nrb * p.KV, p.splits);
+  if (dtype == 0 && p.rowblocks) {
+    if (p.qmax > ATTN_PREFILL_Q || p.splits != 1) return hipErrorInvalidValue;
+    return p.hd == 64    ? launch_prefill<64>(p, s, e0, e1)
+           : p.hd == 128 ? launch_prefill<128>(p, s, e0, e1)
+                         : hipErrorInvalidValue;
+  }
+  if (p.qmax > ATTN_QMAX) return hipErrorInvalidValue;
   if (dtype == 0) {
+    if (!p.row_bt) return hipErrorInvalidValue;
     // a split item's last workgroup merges: every split needs the counter, and
     // the merge holds at most ATTN_MAX_SPLITS partials per query
     if (p.splits > 1 && (!p.cnt || p.splits > ATTN_MAX_SPLITS)) return hipErrorInvalidValue;

@@ -218,12 +218,12 @@ void lay_lane(Alloc& al, Lane& ln, int rows, const Dims& D, int decode_rb, int q
   ln.attn_cnt = al.take<int32_t>(sizeof(int32_t) * std::max(1, ln.attn_items));
 }
 
-// prefill rows per attention row block: as many as fit the 64 query vectors
-// of a workgroup and the default 64 KB of dynamic LDS
+// prefill rows per attention row block: as many as fit the query vectors of a
+// workgroup and (fp32) the default 64 KB of dynamic LDS
 int prefill_qb(const sd_model_cfg& m) {
   const int G = m.n_heads / m.n_kv_heads;
+  if (m.dtype == SD_DTYPE_BF16) return std::max(1, ATTN_PREFILL_Q / G);
   int qb = std::max(1, ATTN_QMAX / G);
-  if (m.dtype == SD_DTYPE_BF16) return qb;   // the matrix kernel's LDS does not grow with the rows
   while (qb > 1 && attention_lds_bytes(m.head_dim, esize(m.dtype), qb * G) > 64 * 1024) --qb;
   return qb;
 }

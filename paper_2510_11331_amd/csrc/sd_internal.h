@@ -291,6 +291,7 @@ constexpr int GEMM_MROWS = 64;         // rows per M block (4 MFMA row tiles)
 // attention geometry
 constexpr int ATTN_KEYS = 64;          // keys per LDS chunk
 constexpr int ATTN_QMAX = 64;          // max query vectors per workgroup
+constexpr int ATTN_PREFILL_Q = 128;    // ... of the 16-bit prefill kernel
 constexpr int ATTN_BT_CAP = 2048;      // KV blocks of one key range staged in LDS (32768 positions)
 constexpr int ATTN_MAX_SPLITS = 12;    // key splits per item the matrix kernel merges itself
 constexpr int ATTN_SPLIT_BELOW = 128;  // decode passes with fewer (row block, kv head) items split the keys

@@ -41,3 +41,18 @@ def test_query_tiles_of_grouped_heads(gamma, length):
     say("query tiles", gamma, length)
     draft = synth.ModelShape(1, 128, 2, 2, 256, 1008, "bf16")
     _compare(GQA, draft, synth.prompts(2, [length, length - 99], GQA.vocab), gamma, prefill_rows=2048)
+
+
+MHA128 = synth.ModelShape(2, 256, 2, 2, 512, 1008, "bf16")     # hd 128
+GQA6 = synth.ModelShape(2, 384, 6, 1, 512, 1008, "bf16")       # hd 64, 6 query heads per kv head (21-row blocks)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [GQA.replace(n_layers=2), MHA128, GQA6], ids=["gqa4_hd64", "mha_hd128", "gqa6_hd64"])
+@pytest.mark.parametrize("lens,rows", [((2, 18, 33, 65, 66), 2048), ((130, 129, 1), 100), ((700, 321), 512)])
+def test_prefill_attention_matches_oracle(shape, lens, rows):
+    """Prefill rows of several tasks in one chunk, chunks that start inside a task and inside a row block, key counts
+    around the 16-key blocks and 64-key stages; slots reused after a longer task (values past the last key are stale)."""
+    say("prefill attention", shape, lens, rows)
+    draft = synth.ModelShape(1, 128, 2, 2, 256, 1008, "bf16")
+    _compare(shape, draft, synth.prompts(len(lens), list(lens), shape.vocab), 2, prefill_rows=rows)
