@@ -386,11 +386,30 @@ GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = fal
 // the drafts') up to 128 rows: their grids of 64-column tiles are under 100
 // workgroups that walk the whole K alone, where the skinny GEMM's four waves
 // split it (small QKV at 128 rows 7.4 us against 9.8).
+// Within one block the two are close while the skinny GEMM's plan fits its
+// shape, and the row tiles are used where it does not:
+//   * 49-64 rows, 12.6 M weights and more: its four row tiles leave registers
+//     for 32 columns only (64 rows: 7B QKV 30.0 -> 24.0 us, gate/up 44.4 ->
+//     36.4, LM head 62.4 -> 48.5; 13B LM head 79.3 -> 60.6);
+//   * 17-48 rows, residual projections of 20 M weights and more, whose K split
+//     it limits to 4 ranges of 32 columns (40 rows: 13B down 39.2 -> 26.6, O
+//     15.5 -> 12.6, 7B down 20.4 -> 19.1; 7B O, 16.8 M, 8.8 against 8.9);
+//   * 17-48 rows, gate/up wider than balanced mode holds (256 workgroups of 96
+//     columns; 40 rows: 13B 61.3 -> 48.8).
 // max_split: K ranges the caller can add (1: none).
 bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile, int* ks) {
   *ks = 1;
-  if (dtype != SD_DTYPE_BF16 || M <= GEMM_MROWS || epi == EPI_PART || N % (epi == EPI_SWIGLU ? 32 : 16)) return false;
-  if (epi != EPI_RESID && epi != EPI_STORE && M <= 128 && (size_t)N * K <= 6300000) return false;
+  if (dtype != SD_DTYPE_BF16 || epi == EPI_PART || N % (epi == EPI_SWIGLU ? 32 : 16)) return false;
+  const size_t weights = (size_t)N * K;
+  if (M > GEMM_MROWS) {
+    if (epi != EPI_RESID && epi != EPI_STORE && M <= 128 && weights <= 6300000) return false;
+  } else if (M > 48) {
+    if (weights < 12600000) return false;
+  } else if (M > 16) {
+    if (!(epi == EPI_RESID && weights >= 20000000) && !(epi == EPI_SWIGLU && N > 24576)) return false;
+  } else {
+    return false;
+  }
   *tile = pick_row_tile(M, N, K, epi == EPI_RESID ? max_split : 1, ks);
   return true;
 }
