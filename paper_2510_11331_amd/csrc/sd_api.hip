@@ -391,11 +391,14 @@ GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = fal
 //   * 49-64 rows, 12.6 M weights and more: its four row tiles leave registers
 //     for 32 columns only (64 rows: 7B QKV 30.0 -> 24.0 us, gate/up 44.4 ->
 //     36.4, LM head 62.4 -> 48.5; 13B LM head 79.3 -> 60.6);
-//   * 17-48 rows, residual projections of 20 M weights and more, whose K split
-//     it limits to 4 ranges of 32 columns (40 rows: 13B down 39.2 -> 26.6, O
-//     15.5 -> 12.6, 7B down 20.4 -> 19.1; 7B O, 16.8 M, 8.8 against 8.9);
-//   * 17-48 rows, gate/up wider than balanced mode holds (256 workgroups of 96
-//     columns; 40 rows: 13B 61.3 -> 48.8).
+//   * up to 48 rows, residual projections of 20 M weights and more, whose K
+//     split it limits to 4 ranges (40 rows: 13B down 39.2 -> 26.6, O 15.5 ->
+//     12.6, 7B down 20.4 -> 19.1; but 7B O, 16.8 M, 8.8 against 8.9);
+//   * up to 48 rows, gate/up wider than balanced mode holds (256 workgroups of
+//     96 columns; 40 rows: 13B 61.3 -> 48.8) and QKV wider than one 48-column
+//     tile per CU (verify pass of two 13B layers at 40 rows 427 -> 407).
+// The 7B QKV and the LM heads stay: with them on row tiles too, two 7B layers
+// at 40 rows took 326 us against 312, with the LM head alone 323.
 // max_split: K ranges the caller can add (1: none).
 bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile, int* ks) {
   *ks = 1;
@@ -405,9 +408,8 @@ bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile
     if (epi != EPI_RESID && epi != EPI_STORE && M <= 128 && weights <= 6300000) return false;
   } else if (M > 48) {
     if (weights < 12600000) return false;
-  } else if (M > 16) {
-    if (!(epi == EPI_RESID && weights >= 20000000) && !(epi == EPI_SWIGLU && N > 24576)) return false;
-  } else {
+  } else if (!(epi == EPI_RESID && weights >= 20000000) && !(epi == EPI_SWIGLU && N > 24576) &&
+             !(epi == EPI_QKV && N > 12288 && weights >= 20000000)) {
     return false;
   }
   *tile = pick_row_tile(M, N, K, epi == EPI_RESID ? max_split : 1, ks);

@@ -71,21 +71,17 @@ def test_prefill_chunk_matches_oracle(shape, rows):
             assert err < BOUND, (k, j, err)
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7), (70, 1)])
-def test_batched_verify_matches_oracle(B, gamma):
-    """65 to 264 verified rows: K-split residual projections, an LM head whose last column tile is partial, values of
-    several tasks in one row tile (and, in the 140 rows of the last case's first draft call, every other row inactive)."""
-    say("row tiles, verify", B, gamma)
-    prompts = synth.prompts(B, [5 + k % 7 for k in range(B)], NARROW.vocab)
-    tw, dw = synth.model_weights(NARROW, 5), synth.model_weights(DRAFT, 6)
-    eng = make_engine(NARROW, DRAFT, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
+def _verify(shape, B, gamma):
+    say("row tiles, verify", shape, B, gamma)
+    prompts = synth.prompts(B, [5 + k % 7 for k in range(B)], shape.vocab)
+    tw, dw = synth.model_weights(shape, 5), synth.model_weights(DRAFT, 6)
+    eng = make_engine(shape, DRAFT, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
     _, _, b, z = run_gpu_steps(eng, list(range(B)), prompts, gamma, 1, 9, list(range(B)), keep_logits=True)
     drafts, q = b.draft_tok.cpu().numpy(), b.q.cpu().numpy().astype(np.float64)
     assert eng.check_flags() == 0
     eng.close()
     seqs = [list(p) + [int(t) for t in drafts[k]] for k, p in enumerate(prompts)]
-    ref = om.Model(NARROW, tw).sequence_logits(seqs, gamma + 1)
+    ref = om.Model(shape, tw).sequence_logits(seqs, gamma + 1)
     zd = om.Model(DRAFT, dw).sequence_logits([sq[:-1] for sq in seqs], gamma)
     for k in range(B):
         for i in range(gamma):
@@ -95,3 +91,25 @@ def test_batched_verify_matches_oracle(B, gamma):
         for j in range(gamma + 1):
             err = float(np.abs(z[0, k, j] - ref[k][j]).max() / np.abs(ref[k][j]).max())
             assert err < BOUND, (k, j, err)
+
+
+LONG_FFN = synth.ModelShape(1, 1024, 8, 8, 20480, 1008, "bf16")   # gate/up past balanced mode, 21 M down projection
+WIDE_QKV = synth.ModelShape(1, 4224, 33, 33, 512, 1008, "bf16")    # 12672 QKV columns
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,B,gamma", [(LONG_FFN, 1, 1), (LONG_FFN, 1, 4), (LONG_FFN, 3, 5), (LONG_FFN, 16, 2),
+                                           (LONG_FFN, 7, 6), (LONG_FFN, 16, 3), (WIDE_QKV, 1, 4), (WIDE_QKV, 8, 5),
+                                           (WIDE_QKV, 13, 4)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
+def test_small_pass_of_wide_projections_matches_oracle(shape, B, gamma):
+    """Passes of up to one 64-row block whose wide projections run on row tiles (2 to 65 rows)."""
+    _verify(shape, B, gamma)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7), (70, 1)])
+def test_batched_verify_matches_oracle(B, gamma):
+    """65 to 264 verified rows: K-split residual projections, an LM head whose last column tile is partial, values of
+    several tasks in one row tile (and, in the 140 rows of the last case's first draft call, every other row inactive)."""
+    _verify(NARROW, B, gamma)
