@@ -21,8 +21,7 @@
 // item keeps an online softmax (running max, running sum, rescaled output);
 // when the keys are split (evenly over the item's context), partial (max,
 // sum, output) triples go to a workspace with device-scope stores, and the
-// last split of the item to finish merges them in split order (the fp32
-// kernel leaves the merge to a second kernel).
+// last split of the item to finish merges them in split order.
 //
 // bf16 models (fp16 KV cache, see f16_t): S^T = K Q^T and O^T += V^T P^T on
 // v_mfma_f32_16x16x32_f16; q and p enter the matrix instruction as fp16 hi + lo
@@ -224,16 +223,57 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnParams p) {
     return;
   }
 
-  // key split: partial (output, max, sum) for attn_merge_kernel
-  const size_t item = (size_t)rbk * p.splits;
+  // key split: this workgroup's partial (output, max, sum) goes out with
+  // device-scope accesses, which the L2 of another XCD does not serve stale;
+  // the item's last split to finish (counted once the stores have been waited
+  // for) merges them.  A merge kernel of its own cost a launch per layer and
+  // draft or verify call (tiny pair, prompt and four steps: 1194 -> 1161 us)
+  const size_t base = (size_t)rbk * p.splits * qmax, item = base + (size_t)split * qmax;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) {
     const int qi = qg + NQG * k;
-    if (qi < Qn) p.part_o[((item + split) * qmax + qi) * HD + dd] = o[k];
+    if (qi < Qn)
+      __hip_atomic_store(p.part_o + (item + qi) * HD + dd, o[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   for (int qi = tid; qi < Qn; qi += 256) {
-    p.part_ml[((item + split) * qmax + qi) * 2 + 0] = Ms[qi];
-    p.part_ml[((item + split) * qmax + qi) * 2 + 1] = Ls[qi];
+    __hip_atomic_store(p.part_ml + (item + qi) * 2, Ms[qi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.part_ml + (item + qi) * 2 + 1, Ls[qi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __shared__ int s_last;
+  __builtin_amdgcn_s_waitcnt(0);      // this wave's partial stores have reached device scope
+  __syncthreads();
+  if (tid == 0) {
+    const int old = __hip_atomic_fetch_add(p.cnt + rbk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = old == p.splits - 1;
+    if (last) __hip_atomic_store(p.cnt + rbk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+
+  // merge, in split order: O = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M),
+  // M = max_s m_s; every load of an output element is issued before any is used
+  for (int qi = qg; qi < Qn; qi += NQG) {
+    float ms[ATTN_MAX_SPLITS], ls[ATTN_MAX_SPLITS], os[ATTN_MAX_SPLITS];
+#pragma unroll
+    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) {
+      const size_t it = base + (size_t)(sp < p.splits ? sp : 0) * qmax + qi;
+      ms[sp] = __hip_atomic_load(p.part_ml + it * 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ls[sp] = __hip_atomic_load(p.part_ml + it * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      os[sp] = __hip_atomic_load(p.part_o + it * HD + dd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    float M = -INFINITY, L = 0.f, O = 0.f;
+#pragma unroll
+    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp)
+      if (sp < p.splits) M = fmaxf(M, ms[sp]);
+#pragma unroll
+    for (int sp = 0; sp < ATTN_MAX_SPLITS; ++sp) {
+      if (sp >= p.splits || ms[sp] == -INFINITY) continue;
+      const float w = expf(ms[sp] - M);
+      L += ls[sp] * w;
+      O += os[sp] * w;
+    }
+    emit(qi, L > 0.f ? O / L : 0.f);
   }
 }
 
@@ -808,44 +848,6 @@ __global__ __launch_bounds__(512, 2) void attention_prefill_kernel(AttnParams p)
   }
 }
 
-// Merge of the key splits of every (row block, kv head) item of the fp32
-// kernel, in split order: O = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M),
-// M = max_s m_s.  (The matrix kernel merges its splits itself: the last split
-// of an item to finish reads the others' partials, written with device-scope
-// stores, and no L2 write-back or second launch is needed.)
-template <typename T, int HD>
-__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
-  const int rbk = blockIdx.x, rb = rbk / p.KV, kvh = rbk % p.KV;
-  int row0, nr;
-  if (p.rowblocks) {
-    row0 = p.rowblocks[2 * rb];
-    nr = p.rowblocks[2 * rb + 1];
-  } else {
-    row0 = rb * p.R;
-    nr = p.R;
-  }
-  const int G = p.H / p.KV, Qn = nr * G;
-  const size_t base = (size_t)rbk * p.splits * p.qmax;
-  for (int idx = threadIdx.x; idx < Qn * HD; idx += blockDim.x) {
-    const int qi = idx / HD, d = idx % HD;
-    float M = -INFINITY;
-    for (int sp = 0; sp < p.splits; ++sp) M = fmaxf(M, p.part_ml[(base + (size_t)sp * p.qmax + qi) * 2]);
-    float L = 0.f, O = 0.f;
-    if (M != -INFINITY) {
-      for (int sp = 0; sp < p.splits; ++sp) {
-        const size_t it = base + (size_t)sp * p.qmax + qi;
-        const float m = p.part_ml[it * 2];
-        if (m == -INFINITY) continue;
-        const float w = expf(m - M);
-        L += p.part_ml[it * 2 + 1] * w;
-        O += p.part_o[it * HD + d] * w;
-      }
-    }
-    const int row = row0 + qi / G, h = kvh * G + qi % G;
-    Store<T>::store((T*)p.out, Tile<T>::off(row, h * HD + d, p.H * HD), L > 0.f ? O / L : 0.f);
-  }
-}
-
 hipError_t launch_rope_table(float2* tab, int n_pos, int half, double theta, hipStream_t s) {
   if (n_pos <= 0 || half <= 0) return hipErrorInvalidValue;
   const size_t n = (size_t)n_pos * half;
@@ -864,10 +866,7 @@ static hipError_t launch_attn_t(const AttnParams& p, hipStream_t s, hipEvent_t e
     if (e != hipSuccess) return e;
     attr_bytes = lds;
   }
-  const bool split = p.splits > 1;
-  launch_k(attention_kernel<T, HD>, dim3(p.nrb * p.KV, p.splits), dim3(256), (uint32_t)lds, s, e0,
-           split ? nullptr : e1, p);
-  if (split) launch_k(attn_merge_kernel<T, HD>, dim3(p.nrb * p.KV), dim3(256), 0, s, nullptr, e1, p);
+  launch_k(attention_kernel<T, HD>, dim3(p.nrb * p.KV, p.splits), dim3(256), (uint32_t)lds, s, e0, e1, p);
   return hipGetLastError();
 }
 
@@ -896,11 +895,11 @@ hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t s, hipEv
                          : hipErrorInvalidValue;
   }
   if (p.qmax > ATTN_QMAX) return hipErrorInvalidValue;
+  // a split item's last workgroup merges: every split needs the counter, and
+  // the merge holds at most ATTN_MAX_SPLITS partials per query
+  if (p.splits > 1 && (!p.cnt || p.splits > ATTN_MAX_SPLITS)) return hipErrorInvalidValue;
   if (dtype == 0) {
     if (!p.row_bt) return hipErrorInvalidValue;
-    // a split item's last workgroup merges: every split needs the counter, and
-    // the merge holds at most ATTN_MAX_SPLITS partials per query
-    if (p.splits > 1 && (!p.cnt || p.splits > ATTN_MAX_SPLITS)) return hipErrorInvalidValue;
     // four waves per workgroup for large grids (hd 64: 1024 or more
     // workgroups, hd 128: 2048): two then share a CU, and one's start and
     // merge overlap the other's stream.  13B B = 64 (2560 verify and 1024

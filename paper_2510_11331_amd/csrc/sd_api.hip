@@ -530,8 +530,7 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     // of the 256 compute units idle, into at most as many splits as keep the
     // grid within one workgroup per CU (every split has keys to read: a
     // second round of workgroups would double the pass); the last split of
-    // an item to finish merges them (16-bit caches), or a second kernel
-    // does (fp32)
+    // an item to finish merges them
     int splits = attn_splits;
     const int items = nrb * c.n_kv_heads;
     if (items >= ATTN_SPLIT_BELOW) splits = 1;

@@ -189,7 +189,7 @@ struct AttnParams {
   float* part_o;             // [nrb*KV, splits, Qmax, hd]
   float* part_ml;            // [nrb*KV, splits, Qmax, 2]
   int qmax;                  // max query vectors per (rowblock, kv head)
-  int* cnt;                  // [nrb*KV] arrivals of an item's key splits (16-bit caches; zero between launches)
+  int* cnt;                  // [nrb*KV] arrivals of an item's key splits (zero between launches)
 };
 
 struct SoftmaxParams {
@@ -293,7 +293,7 @@ constexpr int ATTN_KEYS = 64;          // keys per LDS chunk
 constexpr int ATTN_QMAX = 64;          // max query vectors per workgroup
 constexpr int ATTN_PREFILL_Q = 128;    // ... of the 16-bit prefill kernel
 constexpr int ATTN_BT_CAP = 2048;      // KV blocks of one key range staged in LDS (32768 positions)
-constexpr int ATTN_MAX_SPLITS = 12;    // key splits per item the matrix kernel merges itself
+constexpr int ATTN_MAX_SPLITS = 12;    // key splits per item that its last workgroup merges
 constexpr int ATTN_SPLIT_BELOW = 128;  // decode passes with fewer (row block, kv head) items split the keys
 constexpr int MAX_CTX = ATTN_BT_CAP * 16;   // positions a slot may reach
 
