@@ -194,7 +194,8 @@ int sd_init_static(const sd_config *cfg, const sd_weights *target,
  * back to back) goes to slot slots[k] (host).  Allocates KV blocks for
  * lens[k] + max_new[k] + gamma_max positions, runs both models over
  * prompt[:-1] (Section II-A, prefill stage; the target runs the same pass
- * over the prompt) and sets the slot's next input to the last prompt token.
+ * over the prompt), the last layer of each as far as its keys and values, and
+ * sets the slot's next input to the last prompt token.
  * Blocks until done.  SD_ESTATE if a slot is in use, SD_ENOMEM if a pool
  * is short.
  * Resume: after sd_kv_commit the committed state of a task is its prompt

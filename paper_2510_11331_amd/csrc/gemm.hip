@@ -1,6 +1,7 @@
 // Skinny GEMM for the projections of the draft and verify passes:
 // out[M, N] = A[M, K] * W[N, K]^T with M = rows of the pass (a few to a few
-// dozen in decoding, up to 64 per block in prefill), fp32 accumulation.
+// dozen; 64 per block), fp32 accumulation.  Passes of more rows, and wide
+// projections it does not fit, run on the row-tiled GEMM below.
 //
 // The pass is bound by streaming W from HBM, so the kernel is organised
 // around that stream:

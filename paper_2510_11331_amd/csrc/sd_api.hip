@@ -328,7 +328,7 @@ struct GemmPlan {
 //     Without split_ok the output is added in place;
 //   * LM head and other stores: 64-column tiles for 3-tile row blocks, else
 //     32-column (4-tile row blocks take at most 32 columns);
-//   * several 64-row blocks (B >= 32 verify, prefill): 32-column tiles.
+//   * several 64-row blocks (fp32, and what plan_rows leaves): 32-column tiles.
 // K is never split with a cross-workgroup reduction inside the GEMM: that
 // needs a device-scope release per workgroup, which costs more than it saves.
 GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = false) {

@@ -56,3 +56,14 @@ def test_prefill_attention_matches_oracle(shape, lens, rows):
     say("prefill attention", shape, lens, rows)
     draft = synth.ModelShape(1, 128, 2, 2, 256, 1008, "bf16")
     _compare(shape, draft, synth.prompts(len(lens), list(lens), shape.vocab), 2, prefill_rows=rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("gamma", [4, 8])
+def test_query_tiles_of_large_grids(gamma):
+    """1024 (task, kv head) items, the four-wave form, with key ranges on both sides of 512."""
+    say("query tiles, large grid", gamma)
+    shape = synth.ModelShape(1, 2048, 32, 8, 512, 1008, "bf16")
+    draft = synth.ModelShape(1, 128, 2, 2, 256, 1008, "bf16")
+    lens = [600 if k in (0, 77) else 515 - gamma if k == 5 else 3 + k % 40 for k in range(128)]
+    _compare(shape, draft, synth.prompts(128, lens, shape.vocab), gamma, prefill_rows=2048)
