@@ -366,23 +366,21 @@ def replay_ms(graph, n):
     return float(np.median([ev[k].elapsed_time(ev[k + 1]) for k in range(n)]))
 
 
-def gateup_kernel_name(M: int, N: int) -> str:
+# The row-tiled GEMM's tiles in the library's order: MF, NF, WM, WN, KS, NB
+ROW_TILES = ("8, 4, 2, 2, 1, 3", "6, 4, 2, 2, 1, 3", "5, 4, 2, 4, 2, 3", "4, 4, 2, 4, 1, 4", "5, 2, 2, 4, 2, 3",
+             "4, 2, 2, 4, 2, 4", "2, 2, 4, 2, 4, 3", "3, 2, 2, 4, 2, 4", "3, 2, 2, 2, 4, 3", "2, 2, 2, 4, 2, 4",
+             "1, 2, 4, 2, 4, 4")
+
+
+def gateup_kernel_name(M: int, N: int, K: int) -> str:
     """Kernel the library launches for a bf16 SwiGLU gate/up projection of M
-    rows and N = 2 d_ffn columns (the tile choices of plan_gemm / plan_rows)."""
-    if M > 64 and N >= 8192:
-        best, pad = 6, 1 << 30
-        if M <= 640:
-            for c in (4, 5, 6):
-                rows = -(-M // (32 * c)) * 32 * c
-                if rows <= pad:
-                    best, pad = c, rows
-        mtiles = -(-M // (32 * best))
-        nf = 4 if N % 128 == 0 and mtiles * (N // 128) >= 128 else 2
-        grid = mtiles * N // (32 * nf)
-        waves = 8 if grid <= 256 and best != 8 else 4      # one workgroup per CU: 8 waves
-        spare = 1 if waves == 8 and (best % 2 or nf % 2) else 0
-        nb = (4 if 159 // (4 * best + 4 * nf + spare) >= 4 else 3) if grid <= 256 else 2   # LDS stages
-        return f"gemm_rows_kernel<{best}, {nf}, 2, {nb}, {waves}>"
+    rows, N = 2 d_ffn columns and K = d_model (the rules of plan_gemm and
+    plan_rows; the row tile from the library's own choice)."""
+    if (M > 128 or (M > 64 and N * K > 6300000) or (48 < M <= 64 and N * K >= 12600000) or (M <= 48 and N > 24576)):
+        import ctypes
+        from paper_2510_11331_amd._lib import lib
+        tile = lib()["_ZN2sd13pick_row_tileEiiiiPi"](M, N, K, 1, ctypes.byref(ctypes.c_int()))
+        return f"gemm_rows_kernel<RowTile<{ROW_TILES[tile]}>, 2>"
     if M > 64:
         return "gemm_kernel<_Float16, 4, 2, 2, 2>"
     mt = -(-M // 16)
@@ -928,7 +926,7 @@ def main():
     copy_gbs = copy_ceiling_gbs()
 
     M = B * (gamma + 1)
-    gu_name = gateup_kernel_name(M, 2 * t.d_ffn)
+    gu_name = gateup_kernel_name(M, 2 * t.d_ffn, t.d_model)
     shape_desc = (f"{t.n_layers}-layer d{t.d_model} target ({t.n_heads}/{t.n_kv_heads} heads, FFN {t.d_ffn}) + "
                   f"{d.n_layers}-layer d{d.d_model} draft")
     res = {
