@@ -545,7 +545,9 @@ __device__ __forceinline__ void store_values(const RopeParams& rp, int M, int m0
 // wave's loads visible and frees the buffer stage st - 1 used, which then
 // receives stage st + NB - 1.  Every stage issues the same number of loads
 // (past the last stage with an empty buffer range: they read nothing), so
-// the count the wait uses holds to the end.  The barrier is a plain
+// the count the wait uses holds to the end.  The last stage of a K that is no
+// multiple of 32 KS is partial: its k-steps past K are loaded the same way,
+// as zeros.  The barrier is a plain
 // s_barrier with a compiler memory clobber: a fenced one would wait for
 // every load in flight.  Rows at or past M and columns at or past N load
 // zeros (range-checked buffer loads).  Tile order: every XCD (workgroups are
@@ -577,7 +579,7 @@ __global__ __launch_bounds__(64 * C::WAVES, 2) void gemm_rows_kernel(GemmParams 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % C::WM, wn = wave / C::WM;
   const int r16 = lane & 15, g = lane >> 4;
-  const int ksteps = p.K * 2 / 64, stages = ksteps / KS;
+  const int ksteps = p.K * 2 / 64, stages = (ksteps + KS - 1) / KS;
   const int gz = (p.M + BM - 1) / BM;
   const int ks = max(p.ksplit, 1), R = gz * ks;
   // workgroup w runs on XCD w % 8; XCD x takes the tiles [x T / 8, (x + 1) T / 8) (rounded)
@@ -599,9 +601,12 @@ __global__ __launch_bounds__(64 * C::WAVES, 2) void gemm_rows_kernel(GemmParams 
 
   // this wave's share of a stage: A fragments f = WAVES k + wave (k < LA), W
   // fragments f = WAVES k + wave (k < LW); fragment f = KS t + u is (16-row
-  // tile t, k-step u of the stage).  Indices past the stage's fragments load
-  // nothing (out-of-range offset) into the overflow slot, so every wave
-  // issues the same count
+  // tile t, k-step u of the stage); a wave's fragments are all of k-step
+  // u = wave % KS.  Indices past the stage's fragments load nothing
+  // (out-of-range offset) into the overflow slot, so every wave issues the
+  // same count
+  static_assert(WAVES % KS == 0, "one k-step per wave");
+  const int s_end = min(s_hi, (ksteps - wave % KS + KS - 1) / KS);   // stages in which this wave's k-step exists
   uint32_t aoff[LA], woff[LW];
 #pragma unroll
   for (int k = 0; k < LA; ++k) {
@@ -614,7 +619,7 @@ __global__ __launch_bounds__(64 * C::WAVES, 2) void gemm_rows_kernel(GemmParams 
     woff[k] = f < FW ? (uint32_t)t * tile_bytes + u * 1024u + lane * 16u : OOB;
   }
   auto gload = [&](int st) {
-    const bool ok = st < s_hi;
+    const bool ok = st < s_end;
     const __amdgpu_buffer_rsrc_t ar = buf_rsrc(Ap, ok ? (BM / 16) * tile_bytes : 0u);
     const __amdgpu_buffer_rsrc_t wr = buf_rsrc(Wp, ok ? (uint32_t)ntile * tile_bytes : 0u);
     u32x4* base = lds + (size_t)(st % NB) * FS * 64;

@@ -123,7 +123,7 @@ bool model_ok(const sd_model_cfg& m) {
   if (m.n_heads % m.n_kv_heads) return false;
   if ((m.n_heads / m.n_kv_heads) * 2 > ATTN_QMAX) return false;
   const size_t e = esize(m.dtype);
-  // GEMM K dims stream in 256-byte chunks; N dims come in 16-column tiles
+  // GEMM K dims stream in GEMM_CHUNK = 128-byte chunks; N dims come in 16-column tiles
   if ((m.d_model * e) % GEMM_CHUNK || (m.d_ffn * e) % GEMM_CHUNK) return false;
   if (m.vocab % 16 || m.d_ffn % 16 || m.vocab > 32768) return false;   // row kernels hold <= 32768 entries
   if (!(m.rope_theta > 0.f) || !(m.rms_eps > 0.f)) return false;

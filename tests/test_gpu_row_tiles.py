@@ -71,18 +71,18 @@ def test_prefill_chunk_matches_oracle(shape, rows):
             assert err < BOUND, (k, j, err)
 
 
-def _verify(shape, B, gamma):
-    say("row tiles, verify", shape, B, gamma)
+def _verify(shape, B, gamma, draft=DRAFT):
+    say("row tiles, verify", shape, B, gamma, draft)
     prompts = synth.prompts(B, [5 + k % 7 for k in range(B)], shape.vocab)
-    tw, dw = synth.model_weights(shape, 5), synth.model_weights(DRAFT, 6)
-    eng = make_engine(shape, DRAFT, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
+    tw, dw = synth.model_weights(shape, 5), synth.model_weights(draft, 6)
+    eng = make_engine(shape, draft, tw, dw, max_slots=B, max_batch=B, gamma_max=gamma, max_ctx=64, prefill_rows=256)
     _, _, b, z = run_gpu_steps(eng, list(range(B)), prompts, gamma, 1, 9, list(range(B)), keep_logits=True)
     drafts, q = b.draft_tok.cpu().numpy(), b.q.cpu().numpy().astype(np.float64)
     assert eng.check_flags() == 0
     eng.close()
     seqs = [list(p) + [int(t) for t in drafts[k]] for k, p in enumerate(prompts)]
     ref = om.Model(shape, tw).sequence_logits(seqs, gamma + 1)
-    zd = om.Model(DRAFT, dw).sequence_logits([sq[:-1] for sq in seqs], gamma)
+    zd = om.Model(draft, dw).sequence_logits([sq[:-1] for sq in seqs], gamma)
     for k in range(B):
         for i in range(gamma):
             dlog = np.log(q[k, i]) - zd[k][i]
@@ -113,3 +113,35 @@ def test_batched_verify_matches_oracle(B, gamma):
     """65 to 264 verified rows: K-split residual projections, an LM head whose last column tile is partial, values of
     several tasks in one row tile (and, in the 140 rows of the last case's first draft call, every other row inactive)."""
     _verify(NARROW, B, gamma)
+
+
+# K = 64 (mod 128) in every projection: the last stage of the tiles of four
+# k-steps per stage (6, 8 and 10: 128 x 64, 96 x 64, 64 x 64) is half full
+ODD320 = synth.ModelShape(2, 320, 5, 5, 2752, 1008, "bf16")
+ODD832 = synth.ModelShape(2, 832, 13, 13, 5440, 1008, "bf16")
+ODD192 = synth.ModelShape(2, 192, 3, 1, 64, 1008, "bf16")          # down projection of two k-steps: half a stage
+ODD_LONG = synth.ModelShape(1, 832, 13, 13, 24128, 1008, "bf16")   # 20 M down projection: row tiles from one row on
+ODD_DRAFT = synth.ModelShape(1, 320, 5, 5, 576, 1008, "bf16")
+ODD_CASES = [(ODD320, 65), (ODD320, 512), (ODD320, 1500), (ODD320, 2049), (ODD832, 100), (ODD832, 257), (ODD832, 320),
+             (ODD832, 640), (ODD832, 2049), (ODD192, 127)]
+
+
+def test_odd_k_cases_reach_every_four_step_tile():
+    plans = {p for s, M in ODD_CASES for p in _plans(s, M)}
+    assert {t for _, t, _ in plans} >= {6, 8, 10}
+    assert {(t, k > 1) for e, t, k in plans if e == "resid"} >= {(6, True), (8, True), (10, True), (6, False), (10, False)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,rows", ODD_CASES, ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
+def test_prefill_chunk_of_odd_k_matches_oracle(shape, rows):
+    test_prefill_chunk_matches_oracle(shape, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,B,gamma", [(ODD832, 13, 4), (ODD832, 70, 1), (ODD320, 33, 7), (ODD_LONG, 1, 1),
+                                           (ODD_LONG, 8, 4), (ODD_LONG, 12, 4)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
+def test_verify_and_draft_of_odd_k_match_oracle(shape, B, gamma):
+    """Verify passes of 2 to 264 rows and (B > 32) draft calls of more than one 64-row block."""
+    _verify(shape, B, gamma, ODD_DRAFT)
