@@ -43,6 +43,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 namespace sd {
 
@@ -821,36 +822,45 @@ static hipError_t launch_rows_t(const GemmParams& p, hipStream_t s, hipEvent_t e
 //     us; 7B down projection at M = 2048 190 us (was on the skinny GEMM: 775)
 //   160 x 128 ... 64 x 64 (one per CU, 8 waves, up to 112 KB in flight):
 //     grids near 256 workgroups, with K split where the output is narrow
+// A tile's number is its place in this table; the kernel instances (RowTile)
+// and their dispatch are made from it.
 struct RowTileModel {
-  int bm, bn, per_cu;
+  int mf, nf, wm, wn, ks, nb;   // RowTile
+  int per_cu;
   float e, a, c, h;
+  constexpr int bm() const { return 16 * mf * wm; }
+  constexpr int bn() const { return 16 * nf * wn; }
 };
-static const RowTileModel ROW_TILES[] = {
-    {256, 128, 2, 5.4f, 0.653f, 0.177f, 0.66f}, {192, 128, 2, 4.4f, 0.495f, 0.160f, 0.70f},
-    {160, 256, 1, 4.4f, 0.433f, 0.158f, 1.0f},  {128, 256, 1, 3.5f, 0.379f, 0.125f, 1.0f},
-    {160, 128, 1, 3.1f, 0.264f, 0.088f, 1.0f},  {128, 128, 1, 2.8f, 0.233f, 0.075f, 1.0f},
-    {128, 64, 1, 1.9f, 0.149f, 0.044f, 1.0f},   {96, 128, 1, 2.2f, 0.212f, 0.048f, 1.0f},
-    {96, 64, 1, 1.8f, 0.142f, 0.027f, 1.0f},    {64, 128, 1, 1.7f, 0.163f, 0.046f, 1.0f},
-    {64, 64, 1, 1.5f, 0.101f, 0.029f, 1.0f},
+static constexpr RowTileModel ROW_TILES[] = {
+    {8, 4, 2, 2, 1, 3, 2, 5.4f, 0.653f, 0.177f, 0.66f},   // 256 x 128
+    {6, 4, 2, 2, 1, 3, 2, 4.4f, 0.495f, 0.160f, 0.70f},   // 192 x 128
+    {5, 4, 2, 4, 2, 3, 1, 4.4f, 0.433f, 0.158f, 1.0f},    // 160 x 256
+    {4, 4, 2, 4, 1, 4, 1, 3.5f, 0.379f, 0.125f, 1.0f},    // 128 x 256
+    {5, 2, 2, 4, 2, 3, 1, 3.1f, 0.264f, 0.088f, 1.0f},    // 160 x 128
+    {4, 2, 2, 4, 2, 4, 1, 2.8f, 0.233f, 0.075f, 1.0f},    // 128 x 128
+    {2, 2, 4, 2, 4, 3, 1, 1.9f, 0.149f, 0.044f, 1.0f},    // 128 x 64
+    {3, 2, 2, 4, 2, 4, 1, 2.2f, 0.212f, 0.048f, 1.0f},    // 96 x 128
+    {3, 2, 2, 2, 4, 3, 1, 1.8f, 0.142f, 0.027f, 1.0f},    // 96 x 64
+    {2, 2, 2, 4, 2, 4, 1, 1.7f, 0.163f, 0.046f, 1.0f},    // 64 x 128
+    {1, 2, 4, 2, 4, 4, 1, 1.5f, 0.101f, 0.029f, 1.0f},    // 64 x 64
 };
 constexpr int N_ROW_TILES = sizeof(ROW_TILES) / sizeof(ROW_TILES[0]);
 
+template <int T>
+using RowTileAt = RowTile<ROW_TILES[T].mf, ROW_TILES[T].nf, ROW_TILES[T].wm, ROW_TILES[T].wn, ROW_TILES[T].ks,
+                          ROW_TILES[T].nb>;
+
 template <int EPI>
 static hipError_t launch_rows_e(int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (tile) {   // in the order of ROW_TILES
-    case 0: return launch_rows_t<RowTile<8, 4, 2, 2, 1, 3>, EPI>(p, s, e0, e1);
-    case 1: return launch_rows_t<RowTile<6, 4, 2, 2, 1, 3>, EPI>(p, s, e0, e1);
-    case 2: return launch_rows_t<RowTile<5, 4, 2, 4, 2, 3>, EPI>(p, s, e0, e1);
-    case 3: return launch_rows_t<RowTile<4, 4, 2, 4, 1, 4>, EPI>(p, s, e0, e1);
-    case 4: return launch_rows_t<RowTile<5, 2, 2, 4, 2, 3>, EPI>(p, s, e0, e1);
-    case 5: return launch_rows_t<RowTile<4, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
-    case 6: return launch_rows_t<RowTile<2, 2, 4, 2, 4, 3>, EPI>(p, s, e0, e1);
-    case 7: return launch_rows_t<RowTile<3, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
-    case 8: return launch_rows_t<RowTile<3, 2, 2, 2, 4, 3>, EPI>(p, s, e0, e1);
-    case 9: return launch_rows_t<RowTile<2, 2, 2, 4, 2, 4>, EPI>(p, s, e0, e1);
-    case 10: return launch_rows_t<RowTile<1, 2, 4, 2, 4, 4>, EPI>(p, s, e0, e1);
-    default: return hipErrorInvalidValue;
-  }
+  hipError_t r = hipErrorInvalidValue;
+  auto at = [&]<int T>() {
+    if (tile == T) r = launch_rows_t<RowTileAt<T>, EPI>(p, s, e0, e1);
+    return tile == T;
+  };
+  [&]<int... T>(std::integer_sequence<int, T...>) {
+    (at.template operator()<T>() || ...);
+  }(std::make_integer_sequence<int, N_ROW_TILES>());
+  return r;
 }
 
 int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
@@ -862,7 +872,7 @@ int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
   for (int t = 0; t < N_ROW_TILES; ++t) {
     const RowTileModel& m = ROW_TILES[t];
     for (int ks = 1; ks <= max_ksplit; ++ks) {
-      const int grid = (M + m.bm - 1) / m.bm * ((N + m.bn - 1) / m.bn) * ks;
+      const int grid = (M + m.bm() - 1) / m.bm() * ((N + m.bn() - 1) / m.bn()) * ks;
       if (ks > 1 && grid > 640) break;      // splitting is for grids that leave CUs idle
       // rounds of 256 per_cu workgroups; the last one holds the share `part`
       const int slots = 256 * m.per_cu, full = grid / slots;
