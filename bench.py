@@ -366,29 +366,19 @@ def replay_ms(graph, n):
     return float(np.median([ev[k].elapsed_time(ev[k + 1]) for k in range(n)]))
 
 
-# The row-tiled GEMM's tiles in the library's order: MF, NF, WM, WN, KS, NB
-ROW_TILES = ("8, 4, 2, 2, 1, 3", "6, 4, 2, 2, 1, 3", "5, 4, 2, 4, 2, 3", "4, 4, 2, 4, 1, 4", "5, 2, 2, 4, 2, 3",
-             "4, 2, 2, 4, 2, 4", "2, 2, 4, 2, 4, 3", "3, 2, 2, 4, 2, 4", "3, 2, 2, 2, 4, 3", "2, 2, 2, 4, 2, 4",
-             "1, 2, 4, 2, 4, 4")
-
-
-def gateup_kernel_name(M: int, N: int, K: int) -> str:
-    """Kernel the library launches for a bf16 SwiGLU gate/up projection of M
-    rows, N = 2 d_ffn columns and K = d_model (the rules of plan_gemm and
-    plan_rows; the row tile from the library's own choice)."""
-    if (M > 128 or (M > 64 and N * K > 6300000) or (48 < M <= 64 and N * K >= 12600000) or (M <= 48 and N > 24576)):
-        import ctypes
-        from paper_2510_11331_amd._lib import lib
-        tile = lib()["_ZN2sd13pick_row_tileEiiiiPi"](M, N, K, 1, ctypes.byref(ctypes.c_int()))
-        return f"gemm_rows_kernel<RowTile<{ROW_TILES[tile]}>, 2>"
-    if M > 64:
-        return "gemm_kernel<_Float16, 4, 2, 2, 2>"
-    mt = -(-M // 16)
-    units = N // 32
-    most = -(-units // 256) * 2
-    if mt == 3 and units >= 256 and most <= 6:
-        return f"gemm_kernel<_Float16, 3, {4 if most <= 4 else 6}, 2, 2> (balanced, 256 workgroups)"
-    return f"gemm_kernel<_Float16, {mt}, {4 if mt == 3 and units < 512 else 2}, 2, 2>"
+def gateup_kernel_name(cfg, M: int) -> str:
+    """Kernel the library launches for the target's SwiGLU gate/up projection
+    over M verified rows, by the library's own plan."""
+    import ctypes
+    from paper_2510_11331_amd import _lib
+    p = _lib.ProjPlan()
+    _lib.check(_lib.lib().sd_plan_projection(ctypes.byref(cfg), _lib.SD_PASS_VERIFY, _lib.SD_PROJ_GATEUP, M,
+                                             ctypes.byref(p)), "sd_plan_projection")
+    if p.tile >= 0:
+        return f"gemm_rows_kernel<RowTile<{p.mf}, {p.nf}, {p.wm}, {p.wn}, {p.ks}, {p.nb}>, 2>"
+    scalar = "_Float16" if cfg.target.dtype == _lib.SD_DTYPE_BF16 else "float"
+    return (f"gemm_kernel<{scalar}, {p.mt}, {p.nt}, 2, 2>"
+            + (f" (balanced, {p.grid} workgroups)" if p.tile_unit else ""))
 
 
 def fit_runtime(out_json: str) -> None:
@@ -926,7 +916,7 @@ def main():
     copy_gbs = copy_ceiling_gbs()
 
     M = B * (gamma + 1)
-    gu_name = gateup_kernel_name(M, 2 * t.d_ffn, t.d_model)
+    gu_name = gateup_kernel_name(eng.cfg, M)
     shape_desc = (f"{t.n_layers}-layer d{t.d_model} target ({t.n_heads}/{t.n_kv_heads} heads, FFN {t.d_ffn}) + "
                   f"{d.n_layers}-layer d{d.d_model} draft")
     res = {

@@ -162,6 +162,27 @@ int sd_pack_linear(const void *src, void *dst, int N, int K, int dtype,
 size_t sd_kv_pool_bytes(const sd_config *cfg, int draft);
 size_t sd_workspace_bytes(const sd_config *cfg);
 
+/* How a projection of a pass runs: the choice the launch itself makes (host
+ * only; the buffers of cfg are not used).  rows: rows of the projection (of
+ * the LM head: B (gamma + 1) when verifying, B when drafting).  SD_PROJ_KV is
+ * the QKV projection of a prefill pass's last layer, which has no query
+ * columns.  SD_EINVAL: invalid configuration, more rows than the pass's
+ * workspace holds, SD_PROJ_KV outside prefill, SD_PROJ_LM_HEAD in it. */
+enum { SD_PASS_VERIFY = 0, SD_PASS_DRAFT = 1, SD_PASS_PREFILL = 2, SD_PASS_PREFILL_DRAFT = 3 };
+enum { SD_PROJ_QKV = 0, SD_PROJ_KV = 1, SD_PROJ_O = 2, SD_PROJ_GATEUP = 3, SD_PROJ_DOWN = 4, SD_PROJ_LM_HEAD = 5 };
+typedef struct sd_proj_plan {
+    int M, N, K;
+    int ksplit;                     /* K ranges over workgroups (1: none)   */
+    int grid;                       /* workgroups                           */
+    int tile;                       /* row-tiled GEMM: tile number, else -1 */
+    int mf, nf, wm, wn, ks, nb;     /* ... of (16 mf wm) x (16 nf wn) outputs, wm x wn waves,
+                                     * nb stages of ks 32-entry k-steps in LDS */
+    int mt, nt, kw, tile_unit;      /* skinny GEMM: 16 mt rows x 16 nt columns, kw waves; tile_unit > 0:
+                                     * columns dealt evenly in units of that many 16-column tiles */
+} sd_proj_plan;
+int sd_plan_projection(const sd_config *cfg, int pass, int proj, int rows,
+                       sd_proj_plan *out);
+
 /* Validate cfg, borrow the buffers, clear the workspace's device state.
  * On success *out holds a new context.  The workspace then belongs to the
  * context until sd_destroy: besides scratch it holds slot state and the

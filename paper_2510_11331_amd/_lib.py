@@ -17,7 +17,7 @@ SD_DTYPE_BF16, SD_DTYPE_F32 = 0, 1
  SD_PROF_VERIFY, SD_PROF_DRAFT) = range(5)
 
 # the symbols include/sd.h and include/sd_sched.h declare (checked by the CPU test suite)
-EXPORTS = ("sd_kv_pool_bytes", "sd_workspace_bytes", "sd_init", "sd_init_static", "sd_prefill", "sd_release",
+EXPORTS = ("sd_kv_pool_bytes", "sd_workspace_bytes", "sd_plan_projection", "sd_init", "sd_init_static", "sd_prefill", "sd_release",
            "sd_draft_step", "sd_verify", "sd_accept_resample", "sd_kv_commit", "sd_force_draft", "sd_slot_state",
            "sd_check", "sd_profile", "sd_profile_read", "sd_destroy", "sd_strerror", "sd_last_error",
            "sd_pack_linear", "sd_sched_latency", "sd_sched_batching", "sd_sched_plan", "sd_sched_uplink")
@@ -44,6 +44,15 @@ class Config(C.Structure):
                 ("prefill_rows", C.c_int), ("temperature", C.c_float), ("greedy", C.c_int),
                 ("kv_pool_target", C.c_void_p), ("kv_pool_draft", C.c_void_p),
                 ("workspace", C.c_void_p), ("workspace_bytes", C.c_size_t)]
+
+
+(SD_PASS_VERIFY, SD_PASS_DRAFT, SD_PASS_PREFILL, SD_PASS_PREFILL_DRAFT) = range(4)
+(SD_PROJ_QKV, SD_PROJ_KV, SD_PROJ_O, SD_PROJ_GATEUP, SD_PROJ_DOWN, SD_PROJ_LM_HEAD) = range(6)
+
+
+class ProjPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("M", "N", "K", "ksplit", "grid", "tile", "mf", "nf", "wm", "wn", "ks", "nb", "mt",
+                                       "nt", "kw", "tile_unit")]
 
 
 class SchedModel(C.Structure):
@@ -86,6 +95,7 @@ def lib():
     sig = {
         "sd_kv_pool_bytes": (C.c_size_t, [C.POINTER(Config), I]),
         "sd_workspace_bytes": (C.c_size_t, [C.POINTER(Config)]),
+        "sd_plan_projection": (I, [C.POINTER(Config), I, I, I, C.POINTER(ProjPlan)]),
         "sd_init": (I, [C.POINTER(Config), C.POINTER(Weights), C.POINTER(Weights), C.POINTER(P)]),
         "sd_init_static": (I, [C.POINTER(Config), C.POINTER(Weights), C.POINTER(Weights), C.POINTER(P)]),
         "sd_prefill": (I, [P, I, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32),

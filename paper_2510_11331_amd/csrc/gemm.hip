@@ -846,6 +846,11 @@ static constexpr RowTileModel ROW_TILES[] = {
 };
 constexpr int N_ROW_TILES = sizeof(ROW_TILES) / sizeof(ROW_TILES[0]);
 
+RowTileShape row_tile_shape(int tile) {
+  const RowTileModel& m = ROW_TILES[tile];
+  return {m.mf, m.nf, m.wm, m.wn, m.ks, m.nb};
+}
+
 template <int T>
 using RowTileAt = RowTile<ROW_TILES[T].mf, ROW_TILES[T].nf, ROW_TILES[T].wm, ROW_TILES[T].wn, ROW_TILES[T].ks,
                           ROW_TILES[T].nb>;

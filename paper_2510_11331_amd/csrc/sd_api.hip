@@ -416,6 +416,26 @@ bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile
   return true;
 }
 
+// How one projection runs; max_split > 1 allows the K-split form for EPI_RESID
+struct ProjPlan {
+  bool rows;      // row-tiled GEMM with `tile`, else the skinny GEMM with g
+  int tile, ksplit;
+  GemmPlan g;
+};
+ProjPlan plan_projection(int M, int N, int K, int dtype, size_t esz, int epi, int max_split) {
+  ProjPlan r{};
+  r.rows = plan_rows(M, N, K, dtype, epi, max_split, &r.tile, &r.ksplit);
+  if (!r.rows) {
+    r.g = plan_gemm(M, N, K, esz, epi, max_split >= SKINNY_MAX_KSPLIT);
+    r.ksplit = r.g.ksplit;
+  }
+  return r;
+}
+
+// K ranges of a residual projection over M rows whose partial sums the lane
+// holds (MAX_KSPLIT of them at part_rows rows)
+int residual_splits(int part_rows, int M) { return std::min(MAX_KSPLIT, MAX_KSPLIT * part_rows / M); }
+
 // Launch one projection.  max_split > 1 allows the K-split form for EPI_RESID
 // (part holds max_split partial sums): then *nsplit receives the number of partial sums written to part
 // ([nsplit, M, ldo]) instead of being added to out, and the caller's RMSNorm
@@ -423,11 +443,11 @@ bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile
 int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, int M, int N, int K,
          float* out, int ldo, void* out_t, hipStream_t s, int prof_kind, int prof_kind2,
          const RopeParams* rope = nullptr, float* part = nullptr, int max_split = 1, int* nsplit = nullptr) {
-  int tile = 0, rks = 1;
-  const bool rows = plan_rows(M, N, K, m.c.dtype, epi, max_split, &tile, &rks);
-  GemmPlan g = plan_gemm(M, N, K, m.esz, epi, !rows && max_split >= SKINNY_MAX_KSPLIT);
+  const ProjPlan pl = plan_projection(M, N, K, m.c.dtype, m.esz, epi, max_split);
+  const GemmPlan& g = pl.g;
+  const bool rows = pl.rows;
   if (!rows && !g.tu && N % (16 * g.nt)) return SD_EINVAL;
-  const int ksplit = rows ? rks : g.ksplit;
+  const int ksplit = pl.ksplit;
   if (nsplit) *nsplit = 0;
   if (ksplit > 1) {
     epi = EPI_PART;
@@ -444,7 +464,7 @@ int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, i
   p.ldo = ldo;
   p.out_t = out_t;
   p.tile_unit = rows ? 0 : g.tu;
-  p.ksplit = rows ? rks : 0;
+  p.ksplit = rows ? ksplit : 0;
   if (rope) p.rope = *rope;
   const double out_bytes = epi == EPI_SWIGLU ? (double)M * (N / 2) * m.esz
                            : epi == EPI_QKV  ? (double)M * (m.nq() * 4 + (N - m.nq()) * m.esz)
@@ -454,7 +474,7 @@ int gemm(sd_ctx* ctx, const ModelRT& m, int epi, const void* A, const void* W, i
   ProfRec r1;
   prof_begin(ctx, s, r1, prof_kind, prof_kind2, bytes, true);
   if (rows)
-    HIPCHK(launch_gemm_rows(epi, tile, p, s, r1.a, r1.b));
+    HIPCHK(launch_gemm_rows(epi, pl.tile, p, s, r1.a, r1.b));
   else
     HIPCHK(launch_gemm(m.c.dtype == SD_DTYPE_F32 ? 1 : 0, epi, g.nt, g.mt, g.kw, g.gx, g.ksplit, g.gz, p, s, r1.a,
                        r1.b));
@@ -551,9 +571,9 @@ int forward(sd_ctx* ctx, ModelRT& m, Lane& ln, RowsParams rows, int M, int nrb, 
     prof_begin(ctx, s, ra, verify ? SD_PROF_ATTN_VERIFY : -1, -1, 0, true);
     HIPCHK(launch_attention(dt, ap, s, ra.a, ra.b));
     prof_end(ctx, s, ra);
-    // residual projections may leave K-split partial sums in ln.part (sized
-    // for MAX_KSPLIT of them at part_rows rows) for the RMSNorm after them to add
-    const int max_split = std::min(MAX_KSPLIT, MAX_KSPLIT * ln.part_rows / M);
+    // residual projections may leave K-split partial sums in ln.part for the
+    // RMSNorm after them to add
+    const int max_split = residual_splits(ln.part_rows, M);
     rc = gemm(ctx, m, EPI_RESID, ln.att, m.wo[l], M, d, m.nq(), ln.x, d, nullptr, s, pk_all, -1, nullptr,
               ln.part, max_split, &ns);
     if (rc) return rc;
@@ -659,6 +679,56 @@ size_t sd_kv_pool_bytes(const sd_config* cfg, int draft) {
 size_t sd_workspace_bytes(const sd_config* cfg) {
   if (!cfg_ok(cfg)) return 0;
   return layout(cfg, nullptr);
+}
+
+int sd_plan_projection(const sd_config* cfg, int pass, int proj, int rows, sd_proj_plan* out) {
+  if (!out || !cfg_ok(cfg) || rows < 1) return SD_EINVAL;
+  if (pass < SD_PASS_VERIFY || pass > SD_PASS_PREFILL_DRAFT) return SD_EINVAL;
+  const bool prefill = pass >= SD_PASS_PREFILL;
+  const sd_model_cfg& c = pass == SD_PASS_VERIFY || pass == SD_PASS_PREFILL ? cfg->target : cfg->draft;
+  sd_ctx sizes;
+  layout(cfg, &sizes);
+  const Lane& ln = pass == SD_PASS_DRAFT ? sizes.ld : sizes.lv;
+  if (rows > ln.rows) return SD_EINVAL;
+  const int d = c.d_model, nq = c.n_heads * c.head_dim, nkv = 2 * c.n_kv_heads * c.head_dim;
+  int N = 0, K = d, epi = EPI_STORE, max_split = 1;
+  switch (proj) {
+    case SD_PROJ_QKV: N = nq + nkv; epi = EPI_QKV; break;
+    case SD_PROJ_KV: N = nkv; epi = EPI_QKV; break;
+    case SD_PROJ_O: N = d; K = nq; epi = EPI_RESID; break;
+    case SD_PROJ_GATEUP: N = 2 * c.d_ffn; epi = EPI_SWIGLU; break;
+    case SD_PROJ_DOWN: N = d; K = c.d_ffn; epi = EPI_RESID; break;
+    case SD_PROJ_LM_HEAD: N = c.vocab; break;
+    default: return SD_EINVAL;
+  }
+  if ((proj == SD_PROJ_KV && !prefill) || (proj == SD_PROJ_LM_HEAD && prefill)) return SD_EINVAL;
+  if (epi == EPI_RESID) max_split = residual_splits(ln.part_rows, rows);
+  const ProjPlan pl = plan_projection(rows, N, K, c.dtype, esize(c.dtype), epi, max_split);
+  *out = sd_proj_plan{};
+  out->M = rows;
+  out->N = N;
+  out->K = K;
+  out->ksplit = pl.ksplit;
+  if (pl.rows) {
+    const RowTileShape t = row_tile_shape(pl.tile);
+    out->tile = pl.tile;
+    out->mf = t.mf;
+    out->nf = t.nf;
+    out->wm = t.wm;
+    out->wn = t.wn;
+    out->ks = t.ks;
+    out->nb = t.nb;
+    const int bm = 16 * t.mf * t.wm, bn = 16 * t.nf * t.wn;
+    out->grid = (N + bn - 1) / bn * ((rows + bm - 1) / bm) * pl.ksplit;
+  } else {
+    out->tile = -1;
+    out->mt = pl.g.mt;
+    out->nt = pl.g.nt;
+    out->kw = pl.g.kw;
+    out->tile_unit = pl.g.tu;
+    out->grid = pl.g.gx * pl.g.ksplit * pl.g.gz;
+  }
+  return SD_OK;
 }
 
 int sd_init(const sd_config* cfg, const sd_weights* target, const sd_weights* draft, sd_ctx** out) {

@@ -264,6 +264,8 @@ inline void launch_k(K kern, dim3 grid, dim3 block, uint32_t shm, hipStream_t s,
 // (pick_row_tile chooses one, and the number of K ranges up to max_ksplit).
 // N a multiple of 16 (SWIGLU: 32).
 int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit);
+struct RowTileShape { int mf, nf, wm, wn, ks, nb; };   // template arguments of tile's kernel
+RowTileShape row_tile_shape(int tile);
 hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0 = nullptr,
                             hipEvent_t e1 = nullptr);
 // Host-side check of a skinny GEMM launch (launch_gemm rejects what fails it)

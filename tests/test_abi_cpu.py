@@ -98,3 +98,37 @@ def test_context_free_and_null_context_errors():
     assert L.sd_profile(None, 1) == E
     for code in (0, -1, -2, -3, -4):
         assert len(_lib.strerror(code)) >= 2 and _lib.strerror(code) != str(code)
+
+
+def test_plan_projection():
+    """The plan query: shapes and passes of a configuration, refusals, and plans that cover their outputs."""
+    from paper_2510_11331_amd import _lib
+    L = _lib.lib()
+    p = _lib.ProjPlan()
+    plan = lambda c, ps, pj, rows: L.sd_plan_projection(C.byref(c), ps, pj, rows, C.byref(p))
+    t, d = synth.MODELS["small_target"], synth.MODELS["small_draft"]
+    c = make_cfg(t, d, prefill_rows=700)
+    widths = {_lib.SD_PROJ_QKV: lambda m: ((m.n_heads + 2 * m.n_kv_heads) * m.head_dim, m.d_model),
+              _lib.SD_PROJ_KV: lambda m: (2 * m.n_kv_heads * m.head_dim, m.d_model),
+              _lib.SD_PROJ_O: lambda m: (m.d_model, m.d_model), _lib.SD_PROJ_GATEUP: lambda m: (2 * m.d_ffn, m.d_model),
+              _lib.SD_PROJ_DOWN: lambda m: (m.d_model, m.d_ffn), _lib.SD_PROJ_LM_HEAD: lambda m: (m.vocab, m.d_model)}
+    for ps, m in ((_lib.SD_PASS_VERIFY, t), (_lib.SD_PASS_DRAFT, d), (_lib.SD_PASS_PREFILL, t), (_lib.SD_PASS_PREFILL_DRAFT, d)):
+        refused = _lib.SD_PROJ_LM_HEAD if ps >= _lib.SD_PASS_PREFILL else _lib.SD_PROJ_KV
+        for pj, nk in widths.items():
+            for rows in (1, 10, 64) + ((65, 256, 700) if ps != _lib.SD_PASS_DRAFT else ()):
+                rc = plan(c, ps, pj, rows)
+                assert rc == (_lib.SD_EINVAL if pj == refused else _lib.SD_OK), (ps, pj, rows)
+                if rc != _lib.SD_OK:
+                    continue
+                assert (p.M, (p.N, p.K)) == (rows, nk(m)) and 1 <= p.ksplit <= 6
+                if p.tile >= 0:
+                    bm, bn = 16 * p.mf * p.wm, 16 * p.nf * p.wn
+                    assert p.grid == -(-p.N // bn) * -(-rows // bm) * p.ksplit
+                else:
+                    assert p.tile_unit or p.grid * 16 * p.nt >= p.N * p.ksplit * -(-rows // (16 * p.mt))
+        assert plan(c, ps, _lib.SD_PROJ_QKV, 0) == _lib.SD_EINVAL
+        assert plan(c, ps, _lib.SD_PROJ_QKV, 705) == _lib.SD_EINVAL     # the workspace holds 704 (64 drafting) rows
+    assert plan(c, 4, 0, 1) == plan(c, 0, 6, 1) == plan(c, -1, 0, 1) == plan(c, 0, -1, 1) == _lib.SD_EINVAL
+    assert plan(make_cfg(prefill_rows=0), 0, 0, 1) == _lib.SD_EINVAL
+    f32 = make_cfg()
+    assert plan(f32, _lib.SD_PASS_PREFILL, _lib.SD_PROJ_GATEUP, 64) == _lib.SD_OK and p.tile == -1

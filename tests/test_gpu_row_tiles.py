@@ -9,6 +9,7 @@ import pytest
 import synth
 from oracle import model as om
 from paper_2510_11331_amd import _lib
+from paper_2510_11331_amd.engine import model_cfg
 from sdcase import make_engine, run_gpu_steps, say
 
 WIDE = synth.ModelShape(2, 1024, 8, 8, 11008, 1008, "bf16")
@@ -23,30 +24,41 @@ CASES = [(WIDE, 65), (WIDE, 129), (WIDE, 161), (WIDE, 257), (WIDE, 330), (WIDE, 
 BOUND = 2.0 ** -11 * 6.5
 
 
-def _pick(M, N, K, max_split):
-    f = _lib.lib()["_ZN2sd13pick_row_tileEiiiiPi"]
-    ks = C.c_int()
-    return f(M, N, K, max_split, C.byref(ks)), ks.value
+EPI = ("qkv", "kv", "resid", "gateup", "resid", "store")       # by SD_PROJ_*
+DECODE = (_lib.SD_PROJ_QKV, _lib.SD_PROJ_O, _lib.SD_PROJ_GATEUP, _lib.SD_PROJ_DOWN, _lib.SD_PROJ_LM_HEAD)
+PREFILL = (_lib.SD_PROJ_QKV, _lib.SD_PROJ_KV, _lib.SD_PROJ_O, _lib.SD_PROJ_GATEUP, _lib.SD_PROJ_DOWN)
 
 
-def _plans(shape, M):
-    """(epilogue, tile, K split) of a chunk of M rows; partial sums: six of up to 640 rows."""
-    hd = shape.d_model // shape.n_heads
-    mx = min(6, 6 * min((M + 63) // 64 * 64, 640) // M)
-    return [("qkv", *_pick(M, shape.d_model + 2 * shape.n_kv_heads * hd, shape.d_model, 1)),
-            ("resid", *_pick(M, shape.d_model, shape.d_model, mx)), ("gateup", *_pick(M, 2 * shape.d_ffn, shape.d_model, 1)),
-            ("resid", *_pick(M, shape.d_model, shape.d_ffn, mx))]
+def _config(shape, draft, **kw):
+    c = _lib.Config()
+    c.target, c.draft = model_cfg(shape), model_cfg(draft)
+    c.max_slots = c.max_batch = kw.get("batch", 3)
+    c.gamma_max, c.max_ctx, c.kv_block, c.temperature = kw.get("gamma", 1), 4096, 16, 1.0
+    c.prefill_rows, c.kv_blocks_target, c.kv_blocks_draft = kw.get("prefill_rows", 256), 64, 64
+    return c
+
+
+def _plan(cfg, pass_, proj, rows):
+    p = _lib.ProjPlan()
+    _lib.check(_lib.lib().sd_plan_projection(C.byref(cfg), pass_, proj, rows, C.byref(p)), "sd_plan_projection")
+    return p
+
+
+def _row_tiled(cfg, pass_, rows):
+    """(epilogue, tile, K split) of a pass's projections that run on row tiles."""
+    plans = [(EPI[j], _plan(cfg, pass_, j, rows)) for j in (PREFILL if pass_ >= _lib.SD_PASS_PREFILL else DECODE)]
+    return [(e, p.tile, p.ksplit) for e, p in plans if p.tile >= 0]
+
+
+def _plans(shape, M, draft=DRAFT):
+    """Those of a prefill chunk of M rows."""
+    return _row_tiled(_config(shape, draft, prefill_rows=M), _lib.SD_PASS_PREFILL, M)
 
 
 def test_cases_reach_every_tile():
     plans = [p for s, M in CASES for p in _plans(s, M)]
     assert {t for _, t, _ in plans} == set(range(11))
     assert {k for _, _, k in plans} >= {1, 2, 3, 4, 5, 6}
-    assert _pick(2048, 4096, 11008, 1)[1] == 1
-    # a K range is never shorter than a stage of any tile (128 fp16)
-    for M in (65, 300, 640):
-        for K in (128, 256, 384, 640):
-            assert _pick(M, 128, K, 6)[1] <= K // 64
 
 
 @pytest.mark.gpu
