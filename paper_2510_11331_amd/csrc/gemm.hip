@@ -868,10 +868,18 @@ static hipError_t launch_rows_e(int tile, const GemmParams& p, hipStream_t s, hi
   return r;
 }
 
+// K ranges are dealt in whole stages (kps k-steps each), the same number to
+// every range but the last.  A split is used only if that leaves none empty: an
+// empty range's workgroups would write zeros for the RMSNorm to read.
+static bool row_splits_ok(int ksteps, int kps, int ksplit) {
+  const int stages = (ksteps + kps - 1) / kps, sps = (stages + ksplit - 1) / ksplit;
+  return (ksplit - 1) * sps < stages;
+}
+
 int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
   const int ksteps = K * 2 / 64;
-  // a split range holds at least one stage of every tile (GEMM_CHUNK bytes of K)
-  max_ksplit = std::max(1, std::min(max_ksplit, (int)((size_t)K * 2 / GEMM_CHUNK)));
+  max_ksplit = std::max(1, max_ksplit);
+  *ksplit = 1;
   int best = 0;
   double best_t = 1e30;
   for (int t = 0; t < N_ROW_TILES; ++t) {
@@ -879,6 +887,7 @@ int pick_row_tile(int M, int N, int K, int max_ksplit, int* ksplit) {
     for (int ks = 1; ks <= max_ksplit; ++ks) {
       const int grid = (M + m.bm() - 1) / m.bm() * ((N + m.bn() - 1) / m.bn()) * ks;
       if (ks > 1 && grid > 640) break;      // splitting is for grids that leave CUs idle
+      if (!row_splits_ok(ksteps, m.ks, ks)) continue;
       // rounds of 256 per_cu workgroups; the last one holds the share `part`
       const int slots = 256 * m.per_cu, full = grid / slots;
       const double part = (double)(grid - full * slots) / slots, one = 1.0 / m.per_cu;
@@ -910,8 +919,9 @@ static bool qkv_shape_ok(const GemmParams& p) {
 hipError_t launch_gemm_rows(int epi, int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (tile < 0 || tile >= N_ROW_TILES || p.N % 16 || p.M < 1 || ((size_t)p.K * 2) % GEMM_CHUNK)
     return hipErrorInvalidValue;
-  // a K split writes partial sums (PART) and needs at least one stage per range
-  if (p.ksplit > 1 && (epi != EPI_PART || p.ksplit > (int)((size_t)p.K * 2 / GEMM_CHUNK))) return hipErrorInvalidValue;
+  // a K split writes partial sums (PART)
+  if (p.ksplit > 1 && (epi != EPI_PART || !row_splits_ok(p.K * 2 / 64, ROW_TILES[tile].ks, p.ksplit)))
+    return hipErrorInvalidValue;
   if (epi == EPI_PART && p.ksplit < 1) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_STORE: return launch_rows_e<EPI_STORE>(tile, p, s, e0, e1);

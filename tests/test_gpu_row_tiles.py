@@ -61,6 +61,27 @@ def test_cases_reach_every_tile():
     assert {k for _, _, k in plans} >= {1, 2, 3, 4, 5, 6}
 
 
+def test_no_k_range_is_empty():
+    """Every range of a K split holds at least one of its tile's stages, in all the passes of the workloads and of narrow
+    models whose K is a few stages."""
+    shapes = [(w.target, w.draft) for w in synth.WORKLOADS.values() if w.target.dtype == "bf16"]
+    shapes += [(synth.ModelShape(2, d, d // 64, d // 64, F, 1008, "bf16"), DRAFT)
+               for d, F in ((64, 64), (128, 128), (192, 448), (256, 320), (320, 2752), (640, 704), (832, 5440))]
+    split = 0
+    for t, d in shapes:
+        c = _config(t, d, batch=128, prefill_rows=2048)
+        for ps, most in ((_lib.SD_PASS_VERIFY, 256), (_lib.SD_PASS_DRAFT, 256), (_lib.SD_PASS_PREFILL, 2048),
+                         (_lib.SD_PASS_PREFILL_DRAFT, 2048)):
+            for rows in list(range(1, 257)) + list(range(257, most + 1, 7)):
+                for proj in (_lib.SD_PROJ_O, _lib.SD_PROJ_DOWN):
+                    p = _plan(c, ps, proj, rows)
+                    if p.tile >= 0 and p.ksplit > 1:
+                        stages = -(-p.K // (32 * p.ks))
+                        assert (p.ksplit - 1) * -(-stages // p.ksplit) < stages, (t, ps, proj, rows, p.tile, p.ksplit)
+                        split += 1
+    assert split > 1000
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,rows", CASES, ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
 def test_prefill_chunk_matches_oracle(shape, rows):
