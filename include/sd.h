@@ -183,7 +183,9 @@ typedef struct sd_proj_plan {
 int sd_plan_projection(const sd_config *cfg, int pass, int proj, int rows,
                        sd_proj_plan *out);
 
-/* Validate cfg, borrow the buffers, clear the workspace's device state.
+/* Validate cfg, borrow the buffers, clear the workspace's device state, and
+ * raise the kernels' LDS limits on the current device, which is the device
+ * the context's calls run on.
  * On success *out holds a new context.  The workspace then belongs to the
  * context until sd_destroy: besides scratch it holds slot state and the
  * attention's key-split counters, which every launch leaves at zero, so the

@@ -859,29 +859,28 @@ hipError_t launch_rope_table(float2* tab, int n_pos, int half, double theta, hip
 template <typename T, int HD>
 static hipError_t launch_attn_t(const AttnParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const size_t lds = attn_lds_bytes(HD, sizeof(T), p.qmax);
-  static size_t attr_bytes = 64 * 1024;     // launches above the default limit raise it first
-  if (lds > attr_bytes) {
-    hipError_t e = hipFuncSetAttribute((const void*)attention_kernel<T, HD>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_bytes = lds;
-  }
   launch_k(attention_kernel<T, HD>, dim3(p.nrb * p.KV, p.splits), dim3(256), (uint32_t)lds, s, e0, e1, p);
   return hipGetLastError();
 }
 
+template <int HD> constexpr int PF_LDS = 2 * PF_KEYS * 2 * HD * (int)sizeof(f16_t);
+
 template <int HD>
 static hipError_t launch_prefill(const AttnParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  constexpr int lds = 2 * PF_KEYS * 2 * HD * (int)sizeof(f16_t);
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)attention_prefill_kernel<HD>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
-  launch_k(attention_prefill_kernel<HD>, dim3(p.nrb * p.KV), dim3(512), (uint32_t)lds, s, e0, e1, p);
+  launch_k(attention_prefill_kernel<HD>, dim3(p.nrb * p.KV), dim3(512), (uint32_t)PF_LDS<HD>, s, e0, e1, p);
   return hipGetLastError();
+}
+
+hipError_t prepare_attention() {
+  hipError_t r = hipSuccess;
+  auto limit = [&](const void* kern, size_t lds) {
+    if (r == hipSuccess) r = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  };
+  limit((const void*)attention_prefill_kernel<64>, PF_LDS<64>);
+  limit((const void*)attention_prefill_kernel<128>, PF_LDS<128>);
+  limit((const void*)attention_kernel<float, 64>, attn_lds_bytes(64, sizeof(float), ATTN_QMAX));
+  limit((const void*)attention_kernel<float, 128>, attn_lds_bytes(128, sizeof(float), ATTN_QMAX));
+  return r;
 }
 
 hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

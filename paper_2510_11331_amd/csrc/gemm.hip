@@ -792,13 +792,6 @@ __global__ __launch_bounds__(64 * C::WAVES, 2) void gemm_rows_kernel(GemmParams 
 
 template <typename C, int EPI>
 static hipError_t launch_rows_t(const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<C, EPI>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
   const int grid = (p.N + C::BN - 1) / C::BN * ((p.M + C::BM - 1) / C::BM) * std::max(p.ksplit, 1);
   launch_k(gemm_rows_kernel<C, EPI>, dim3(grid), dim3(64 * C::WAVES), C::LDS, s, e0, e1, p);
   return hipGetLastError();
@@ -854,6 +847,21 @@ RowTileShape row_tile_shape(int tile) {
 template <int T>
 using RowTileAt = RowTile<ROW_TILES[T].mf, ROW_TILES[T].nf, ROW_TILES[T].wm, ROW_TILES[T].wn, ROW_TILES[T].ks,
                           ROW_TILES[T].nb>;
+
+hipError_t prepare_gemm_rows() {
+  hipError_t r = hipSuccess;
+  auto limit = [&]<int T, int EPI>() {
+    if (r == hipSuccess)
+      r = hipFuncSetAttribute((const void*)gemm_rows_kernel<RowTileAt<T>, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)RowTileAt<T>::LDS);
+  };
+  [&]<int... T>(std::integer_sequence<int, T...>) {
+    ((limit.template operator()<T, EPI_STORE>(), limit.template operator()<T, EPI_RESID>(),
+      limit.template operator()<T, EPI_SWIGLU>(), limit.template operator()<T, EPI_QKV>(),
+      limit.template operator()<T, EPI_PART>()), ...);
+  }(std::make_integer_sequence<int, N_ROW_TILES>());
+  return r;
+}
 
 template <int EPI>
 static hipError_t launch_rows_e(int tile, const GemmParams& p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

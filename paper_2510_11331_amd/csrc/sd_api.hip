@@ -750,10 +750,11 @@ int sd_init(const sd_config* cfg, const sd_weights* target, const sd_weights* dr
   ctx->slots.resize(cfg->max_slots);
   for (int b = cfg->kv_blocks_target - 1; b >= 0; --b) ctx->free_t.push_back(b);
   for (int b = cfg->kv_blocks_draft - 1; b >= 0; --b) ctx->free_d.push_back(b);
-  // device state: invalid slots, no errors; rotary tables
-  // (kernels, synchronous here)
+  // LDS limits of the context's device; device state: invalid slots, no
+  // errors; rotary tables (kernels, synchronous here)
   hipStream_t s = nullptr;
-  bool ok = launch_fill_i32((int32_t*)cfg->workspace, 0, layout(cfg, nullptr) / 4, s) == hipSuccess &&
+  bool ok = prepare_gemm_rows() == hipSuccess && prepare_attention() == hipSuccess &&
+            launch_fill_i32((int32_t*)cfg->workspace, 0, layout(cfg, nullptr) / 4, s) == hipSuccess &&
             launch_rope_table(ctx->tgt.rope_tab, ctx->tgt.rope_pos, cfg->target.head_dim / 2,
                               cfg->target.rope_theta, s) == hipSuccess &&
             launch_rope_table(ctx->dft.rope_tab, ctx->dft.rope_pos, cfg->draft.head_dim / 2,

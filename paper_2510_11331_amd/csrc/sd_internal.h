@@ -259,6 +259,12 @@ inline void launch_k(K kern, dim3 grid, dim3 block, uint32_t shm, hipStream_t s,
   else hipLaunchKernelGGL(kern, grid, block, shm, s, args...);
 }
 
+// Raise the dynamic-LDS limits of the kernels that launch with more than the
+// default on the current device (the limit is an attribute of a kernel on one
+// device), so that launches keep no state: called for every new context.
+hipError_t prepare_gemm_rows();
+hipError_t prepare_attention();
+
 // Row-tiled GEMM (16-bit operands) for passes of more rows than the skinny
 // GEMM's one block: output tile number `tile` of the list in gemm.hip
 // (pick_row_tile chooses one, and the number of K ranges up to max_ksplit).
