@@ -328,7 +328,7 @@ struct GemmPlan {
 //     Without split_ok the output is added in place;
 //   * LM head and other stores: 64-column tiles for 3-tile row blocks, else
 //     32-column (4-tile row blocks take at most 32 columns);
-//   * several 64-row blocks (fp32, and what plan_rows leaves): 32-column tiles.
+//   * several 64-row blocks (fp32, and what use_row_tiles leaves): 32-column tiles.
 // K is never split with a cross-workgroup reduction inside the GEMM: that
 // needs a device-scope release per workgroup, which costs more than it saves.
 GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = false) {
@@ -377,46 +377,55 @@ GemmPlan plan_gemm(int M, int N, int K, size_t esz, int epi, bool split_ok = fal
   return g;
 }
 
-// Whether a projection runs on the row-tiled GEMM (16-bit operands only).
-// Above one 64-row block it does, with the tile and K split of pick_row_tile:
-// the skinny GEMM re-reads the activations for every 32 columns and the
-// weights for every 64 rows (7B residual projections at 2048 rows: O 299 ->
-// 77 us, down 775 -> 190; draft d = 1024 at 2048 rows: down 54 -> 23).  Not the
-// small QKV and gate/up projections (N K up to 6.3 M: the small target's QKV,
-// the drafts') up to 128 rows: their grids of 64-column tiles are under 100
-// workgroups that walk the whole K alone, where the skinny GEMM's four waves
-// split it (small QKV at 128 rows 7.4 us against 9.8).
-// Within one block the two are close while the skinny GEMM's plan fits its
-// shape, and the row tiles are used where it does not:
-//   * 49-64 rows, 12.6 M weights and more: its four row tiles leave registers
-//     for 32 columns only (64 rows: 7B QKV 30.0 -> 24.0 us, gate/up 44.4 ->
-//     36.4, LM head 62.4 -> 48.5; 13B LM head 79.3 -> 60.6);
-//   * up to 48 rows, residual projections of 20 M weights and more, whose K
-//     split it limits to 4 ranges (40 rows: 13B down 39.2 -> 26.6, O 15.5 ->
-//     12.6, 7B down 20.4 -> 19.1; but 7B O, 16.8 M, 8.8 against 8.9);
-//   * up to 48 rows, gate/up wider than balanced mode holds (256 workgroups of
-//     96 columns; 40 rows: 13B 61.3 -> 48.8) and QKV wider than one 48-column
-//     tile per CU (verify pass of two 13B layers at 40 rows 427 -> 407).
-// The 7B QKV and the LM heads stay: with them on row tiles too, two 7B layers
-// at 40 rows took 326 us against 312, with the LM head alone 323.
-// max_split: K ranges the caller can add (1: none).
-bool plan_rows(int M, int N, int K, int dtype, int epi, int max_split, int* tile, int* ks) {
-  *ks = 1;
+// Whether a projection runs on the row-tiled GEMM (16-bit operands only)
+// rather than on the skinny GEMM with plan g.  What decides is whether g's grid
+// is one round of workgroups for the 256 CUs: from three 16-row tiles on its
+// register use leaves about one workgroup per CU, and a second, partly filled
+// round costs as much as the first.  Both sides were measured at 200 projection
+// shapes of widths 512 to 8192, the models' and others between them; the ranges
+// are skinny time / row-tile time (above 1 the row tiles are faster; residual
+// projections with the RMSNorm that adds their partial sums):
+//   * above 64 rows residual projections [0.99-2.6, median 1.5] and LM heads
+//     [1.3-2.6]: the skinny GEMM re-reads the activations for every 32 columns
+//     and the weights for every 64 rows.  QKV and gate/up too [1.1-2.9], unless
+//     two row blocks of the skinny GEMM are one round, N <= 4096 [K of 1024 and
+//     more: 0.88-1.1, from 2048 on 0.88-0.95; below, 1 us kernels: 0.86-1.2];
+//   * 49-64 rows: what is more than one round [1.03-1.8; one round 0.72-1.06], and
+//     residual projections of 16 M weights on (K split in more ranges than the
+//     skinny GEMM's four) [0.97-1.18; 9-12 M: 0.97-1.02];
+//   * 33-48 rows: residual projections of more than one round [1.03-1.6] or of
+//     20 M weights on [1.01-1.09; below, one round: 0.90-1.12, median 0.99];
+//   * 17-32 rows: those of 20 M on [0.98-1.4; below 0.84-1.05 in one round,
+//     0.92-1.19 in more];
+//   * up to 16 rows, where the skinny tiles are light: those of 20 M on [0.89-1.19,
+//     median 1.04; below 0.79-1.14, median 0.93].  The lower end is 4096 x 11008
+//     [0.95] and other full skinny rounds; inside a pass, with its activations
+//     just written, that one is no faster there (two 7B layers at 5 rows 248.7
+//     us, on row tiles 247.9);
+//   * up to 48 rows, gate/up past what balanced mode holds (256 workgroups of
+//     96 columns) [33-48 rows 0.95-1.37, median 1.16; up to 32 0.94-1.2, median
+//     1.06]; up to 32 rows only while the row tiles' own grid, 128 columns each,
+//     stays below 256 [32768 columns on: 0.77-1.0];
+//   * up to 48 rows, QKV past one 48-column tile per CU [12289-15360 columns:
+//     1.02-1.5; fewer: 0.52-1.1]; up to 16 rows only while the skinny GEMM uses
+//     those tiles, to 15360 columns [wider: 0.86-1.0].
+// LM heads stay on the skinny GEMM up to 48 rows [K of 2048 and more: 0.86-1.25,
+// median 0.95].
+bool use_row_tiles(int M, int N, int K, int dtype, int epi, const GemmPlan& g) {
   if (dtype != SD_DTYPE_BF16 || epi == EPI_PART || N % (epi == EPI_SWIGLU ? 32 : 16)) return false;
+  const bool resid = epi == EPI_RESID;
   const size_t weights = (size_t)N * K;
-  if (M > GEMM_MROWS) {
-    if (epi != EPI_RESID && epi != EPI_STORE && M <= 128 && weights <= 6300000) return false;
-  } else if (M > 48) {
-    if (weights < 12600000) return false;
-  } else if (!(epi == EPI_RESID && weights >= 20000000) && !(epi == EPI_SWIGLU && N > 24576) &&
-             !(epi == EPI_QKV && N > 12288 && weights >= 20000000)) {
-    return false;
-  }
-  *tile = pick_row_tile(M, N, K, epi == EPI_RESID ? max_split : 1, ks);
-  return true;
+  const int grid = g.gx * g.ksplit * g.gz, rounds = (grid + 255) / 256;
+  if (M > 2 * GEMM_MROWS) return true;
+  if (M > GEMM_MROWS) return resid || epi == EPI_STORE || rounds > 1;
+  if (M > 48) return rounds > 1 || (resid && weights >= 16000000);
+  if (resid) return weights >= 20000000 || (M > 32 && rounds > 1);
+  if (epi == EPI_SWIGLU) return N > 24576 && (M > 32 || N < 32768);
+  return epi == EPI_QKV && N > 12288 && (M > 16 || N <= 15360);
 }
 
-// How one projection runs; max_split > 1 allows the K-split form for EPI_RESID
+// How one projection runs; max_split: K ranges whose partial sums the caller
+// can add (EPI_RESID; 1: none)
 struct ProjPlan {
   bool rows;      // row-tiled GEMM with `tile`, else the skinny GEMM with g
   int tile, ksplit;
@@ -424,11 +433,10 @@ struct ProjPlan {
 };
 ProjPlan plan_projection(int M, int N, int K, int dtype, size_t esz, int epi, int max_split) {
   ProjPlan r{};
-  r.rows = plan_rows(M, N, K, dtype, epi, max_split, &r.tile, &r.ksplit);
-  if (!r.rows) {
-    r.g = plan_gemm(M, N, K, esz, epi, max_split >= SKINNY_MAX_KSPLIT);
-    r.ksplit = r.g.ksplit;
-  }
+  r.g = plan_gemm(M, N, K, esz, epi, max_split >= SKINNY_MAX_KSPLIT);
+  r.ksplit = r.g.ksplit;
+  r.rows = use_row_tiles(M, N, K, dtype, epi, r.g);
+  if (r.rows) r.tile = pick_row_tile(M, N, K, epi == EPI_RESID ? max_split : 1, &r.ksplit);
   return r;
 }
 

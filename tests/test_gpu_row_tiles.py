@@ -61,6 +61,39 @@ def test_cases_reach_every_tile():
     assert {k for _, _, k in plans} >= {1, 2, 3, 4, 5, 6}
 
 
+def test_dispatch_follows_the_grid():
+    """The rules that move a projection between the skinny GEMM and the row tiles, on both sides of each: one round of
+    skinny workgroups for 256 CUs (32 columns and 64 rows each; QKV up to 64 rows 16 columns), the weights from which
+    a residual projection's larger K split pays, and the widths that balanced and 48-column tiles hold."""
+    V, Q, O, GU, DOWN = (_lib.SD_PASS_VERIFY, _lib.SD_PROJ_QKV, _lib.SD_PROJ_O, _lib.SD_PROJ_GATEUP, _lib.SD_PROJ_DOWN)
+    sh = lambda d, H, KV, F: synth.ModelShape(1, d, H, KV, F, 1008, "bf16")
+    cases = [
+        (sh(2048, 32, 16, 2048), Q, {64: 0, 65: 0, 128: 0, 129: 1}),       # 4096 columns: two row blocks are one round
+        (sh(1408, 22, 22, 2112), Q, {48: 0, 49: 1, 65: 1, 128: 1}),        # 4224
+        (sh(2048, 32, 16, 2048), GU, {64: 0, 65: 0, 128: 0, 129: 1}),      # 4096
+        (sh(2048, 32, 16, 2112), GU, {49: 0, 64: 0, 65: 1, 128: 1}),       # 4224: one row block is one round still
+        (sh(2048, 32, 16, 4160), GU, {32: 0, 48: 0, 49: 1, 64: 1}),        # 8320
+        (sh(2048, 16, 16, 5632), O, {8: 0, 40: 0, 64: 0, 65: 1}),          # 4.2 M, 2048 columns: one round
+        (sh(2304, 18, 18, 5632), O, {8: 0, 32: 0, 33: 1, 64: 1}),          # 5.3 M, 2304 columns: more
+        (sh(2048, 16, 16, 7808), DOWN, {64: 0, 65: 1}),                    # 15.99 M weights
+        (sh(2048, 16, 16, 7872), DOWN, {48: 0, 49: 1, 64: 1}),             # 16.1 M
+        (sh(2048, 16, 16, 9728), DOWN, {16: 0, 17: 0, 48: 0, 49: 1}),      # 19.9 M
+        (sh(2048, 16, 16, 9792), DOWN, {1: 1, 16: 1, 17: 1, 48: 1}),       # 20.05 M
+        (sh(1024, 16, 16, 12288), GU, {1: 0, 48: 0, 49: 1}),               # 24576: the most balanced mode holds
+        (sh(1024, 16, 16, 12352), GU, {1: 1, 32: 1, 48: 1}),
+        (sh(1024, 16, 16, 16384), GU, {1: 0, 32: 0, 33: 1}),               # 32768
+        (sh(4096, 32, 32, 64), Q, {1: 0, 48: 0, 49: 1}),                   # 12288
+        (sh(4224, 33, 33, 64), Q, {1: 1, 48: 1}),                          # 12672
+        (sh(5248, 41, 41, 64), Q, {1: 0, 16: 0, 17: 1}),                   # 15744
+    ]
+    for shape, proj, want in cases:
+        c = _config(shape, DRAFT, batch=128)
+        got = {rows: int(_plan(c, V, proj, rows).tile >= 0) for rows in want}
+        assert got == want, (shape, proj, got, want)
+    c = _config(synth.MODELS["tiny_target"].replace(vocab=1008), DRAFT, batch=128)
+    assert all(_plan(c, V, p, r).tile < 0 for p in DECODE for r in (1, 64, 256))      # fp32 has no row tiles
+
+
 def test_no_k_range_is_empty():
     """Every range of a K split holds at least one of its tile's stages, in all the passes of the workloads and of narrow
     models whose K is a few stages."""
@@ -137,6 +170,20 @@ WIDE_QKV = synth.ModelShape(1, 4224, 33, 33, 512, 1008, "bf16")    # 12672 QKV c
                          ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
 def test_small_pass_of_wide_projections_matches_oracle(shape, B, gamma):
     """Passes of up to one 64-row block whose wide projections run on row tiles (2 to 65 rows)."""
+    _verify(shape, B, gamma)
+
+
+ROUTED = [(synth.ModelShape(1, 2048, 32, 16, 2112, 1008, "bf16"), 13, 4),   # 65 rows: QKV skinny, gate/up on row tiles
+          (synth.ModelShape(1, 1536, 24, 24, 512, 1008, "bf16"), 7, 4),     # 35: O
+          (synth.ModelShape(1, 1536, 24, 24, 512, 1008, "bf16"), 10, 4),    # 50: QKV and O
+          (synth.ModelShape(1, 1024, 16, 16, 14336, 1008, "bf16"), 1, 4),   # 5: gate/up of 28672 columns
+          (synth.ModelShape(1, 1024, 16, 16, 14336, 1008, "bf16"), 7, 4)]   # 35
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,B,gamma", ROUTED, ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
+def test_both_sides_of_the_dispatch_match_oracle(shape, B, gamma):
+    assert _row_tiled(_config(shape, DRAFT, batch=B, gamma=gamma), _lib.SD_PASS_VERIFY, B * (gamma + 1))
     _verify(shape, B, gamma)
 
 
