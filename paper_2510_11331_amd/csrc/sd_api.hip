@@ -675,6 +675,24 @@ std::mutex g_static_mu;
 void* g_static_ptr[STATIC_MAX_DEV] = {};
 bool g_static_held[STATIC_MAX_DEV] = {};
 
+// The kernels' LDS limits on the current device, raised by the first context
+// there (59 attribute calls, 45 us, of some 250 us that a context takes).
+std::mutex g_limits_mu;
+bool g_limits_set[STATIC_MAX_DEV] = {};
+
+hipError_t set_lds_limits() {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool kept = dev >= 0 && dev < STATIC_MAX_DEV;
+  std::lock_guard<std::mutex> lock(g_limits_mu);
+  if (kept && g_limits_set[dev]) return hipSuccess;
+  e = prepare_gemm_rows();
+  if (e == hipSuccess) e = prepare_attention();
+  if (kept) g_limits_set[dev] = e == hipSuccess;
+  return e;
+}
+
 // ============================================================== C ABI
 
 extern "C" {
@@ -761,7 +779,7 @@ int sd_init(const sd_config* cfg, const sd_weights* target, const sd_weights* dr
   // LDS limits of the context's device; device state: invalid slots, no
   // errors; rotary tables (kernels, synchronous here)
   hipStream_t s = nullptr;
-  bool ok = prepare_gemm_rows() == hipSuccess && prepare_attention() == hipSuccess &&
+  bool ok = set_lds_limits() == hipSuccess &&
             launch_fill_i32((int32_t*)cfg->workspace, 0, layout(cfg, nullptr) / 4, s) == hipSuccess &&
             launch_rope_table(ctx->tgt.rope_tab, ctx->tgt.rope_pos, cfg->target.head_dim / 2,
                               cfg->target.rope_theta, s) == hipSuccess &&

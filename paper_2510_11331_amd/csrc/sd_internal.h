@@ -261,7 +261,7 @@ inline void launch_k(K kern, dim3 grid, dim3 block, uint32_t shm, hipStream_t s,
 
 // Raise the dynamic-LDS limits of the kernels that launch with more than the
 // default on the current device (the limit is an attribute of a kernel on one
-// device), so that launches keep no state: called for every new context.
+// device): done when a context is made there, so that launches keep no state.
 hipError_t prepare_gemm_rows();
 hipError_t prepare_attention();
 
