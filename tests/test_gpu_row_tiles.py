@@ -1,6 +1,8 @@
-"""Row-tiled GEMM: every output tile, K split and epilogue at row and column
-counts around the tile edges, through prefill chunks of a given number of
-rows (three prompts in one chunk, so row positions jump inside a tile)."""
+"""Row-tiled GEMM against the oracle: every output tile, every pair of tile and
+epilogue that the workloads dispatch, and K splits of 1 to 6, at row and column
+counts around the tile edges, through prefill chunks of a given number of rows
+(three prompts in one chunk, so row positions jump inside a tile), verify passes
+and draft calls.  Which of them run on row tiles is the library's own plan."""
 import ctypes as C
 
 import numpy as np
@@ -163,10 +165,12 @@ LONG_FFN = synth.ModelShape(1, 1024, 8, 8, 20480, 1008, "bf16")   # gate/up past
 WIDE_QKV = synth.ModelShape(1, 4224, 33, 33, 512, 1008, "bf16")    # 12672 QKV columns
 
 
+SMALL_PASSES = [(LONG_FFN, 1, 1), (LONG_FFN, 1, 4), (LONG_FFN, 3, 5), (LONG_FFN, 16, 2), (LONG_FFN, 7, 6), (LONG_FFN, 16, 3),
+                (WIDE_QKV, 1, 4), (WIDE_QKV, 8, 5), (WIDE_QKV, 13, 4)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,B,gamma", [(LONG_FFN, 1, 1), (LONG_FFN, 1, 4), (LONG_FFN, 3, 5), (LONG_FFN, 16, 2),
-                                           (LONG_FFN, 7, 6), (LONG_FFN, 16, 3), (WIDE_QKV, 1, 4), (WIDE_QKV, 8, 5),
-                                           (WIDE_QKV, 13, 4)],
+@pytest.mark.parametrize("shape,B,gamma", SMALL_PASSES,
                          ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}")
 def test_small_pass_of_wide_projections_matches_oracle(shape, B, gamma):
     """Passes of up to one 64-row block whose wide projections run on row tiles (2 to 65 rows)."""
@@ -187,8 +191,11 @@ def test_both_sides_of_the_dispatch_match_oracle(shape, B, gamma):
     _verify(shape, B, gamma)
 
 
+BATCHED = [(13, 4), (24, 4), (33, 7), (70, 1)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,gamma", [(13, 4), (24, 4), (33, 7), (70, 1)])
+@pytest.mark.parametrize("B,gamma", BATCHED)
 def test_batched_verify_matches_oracle(B, gamma):
     """65 to 264 verified rows: K-split residual projections, an LM head whose last column tile is partial, values of
     several tasks in one row tile (and, in the 140 rows of the last case's first draft call, every other row inactive)."""
@@ -225,3 +232,52 @@ def test_prefill_chunk_of_odd_k_matches_oracle(shape, rows):
 def test_verify_and_draft_of_odd_k_match_oracle(shape, B, gamma):
     """Verify passes of 2 to 264 rows and (B > 32) draft calls of more than one 64-row block."""
     _verify(shape, B, gamma, ODD_DRAFT)
+
+
+def _shape(d, H, KV, F, layers=2, vocab=1008):
+    return synth.ModelShape(layers, d, H, KV, F, vocab, "bf16")
+
+
+# The pairs of tile and epilogue of the 7B-, 13B- and small workloads that the cases above leave out, at narrower widths
+PAIR_PREFILL = [(_shape(1024, 8, 8, 512), 801), (_shape(1024, 8, 8, 512), 1281), (_shape(2048, 16, 16, 512), 900),
+                (_shape(2048, 16, 16, 512), 1540), (_shape(2048, 16, 16, 512), 2049), (_shape(2048, 16, 16, 5120), 801),
+                (_shape(2176, 17, 17, 512), 400), (_shape(2176, 17, 17, 5120), 1160), (_shape(3072, 24, 24, 512), 1601),
+                (_shape(3072, 24, 24, 512), 1930), (_shape(3072, 24, 24, 5120), 1030), (_shape(4096, 32, 32, 512), 260),
+                (_shape(4096, 32, 32, 512), 2049)]
+WIDE_HEAD = _shape(128, 2, 2, 512, 1, 32000)
+PAIR_VERIFY = [(17, 5), (19, 6), (26, 6), (33, 7), (49, 7), (65, 7)]          # 102 to 520 rows of 32000 logits
+
+
+def _pairs(cfg, pass_, rows):
+    return {(t, "partial sums" if k > 1 else e) for e, t, k in _row_tiled(cfg, pass_, rows)}
+
+
+def test_cases_cover_the_workloads():
+    """Every (tile, epilogue) that a pass of the bf16 workloads runs on, at any number of rows, is in a GPU case."""
+    V, D, P, PD = _lib.SD_PASS_VERIFY, _lib.SD_PASS_DRAFT, _lib.SD_PASS_PREFILL, _lib.SD_PASS_PREFILL_DRAFT
+    want = set()
+    for w in synth.WORKLOADS.values():
+        if w.target.dtype == "bf16":
+            c = _config(w.target, w.draft, batch=64, gamma=8, prefill_rows=2048)
+            for ps, n in ((V, 576), (D, 128), (P, 2048), (PD, 2048)):
+                want |= set().union(*(_pairs(c, ps, rows) for rows in range(1, n + 1)))
+    have = set()
+    for shape, rows in CASES + ODD_CASES + PAIR_PREFILL:
+        have |= _pairs(_config(shape, DRAFT, prefill_rows=rows), P, rows)
+    for shape, B, gamma in (SMALL_PASSES + ROUTED + [(NARROW, B, g) for B, g in BATCHED]
+                            + [(WIDE_HEAD, B, g) for B, g in PAIR_VERIFY]):
+        c = _config(shape, DRAFT.replace(vocab=shape.vocab), batch=B, gamma=gamma)
+        have |= _pairs(c, V, B * (gamma + 1)) | _pairs(c, D, B) | _pairs(c, D, 2 * B)
+    assert len(want) >= 50 and want <= have, sorted(want - have)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,rows", PAIR_PREFILL, ids=lambda v: str(v) if isinstance(v, int) else f"d{v.d_model}-F{v.d_ffn}")
+def test_prefill_chunk_of_other_tiles_matches_oracle(shape, rows):
+    test_prefill_chunk_matches_oracle(shape, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,gamma", PAIR_VERIFY)
+def test_wide_head_on_row_tiles_matches_oracle(B, gamma):
+    _verify(WIDE_HEAD, B, gamma, DRAFT.replace(vocab=WIDE_HEAD.vocab))
