@@ -664,8 +664,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attention_mfma_kernel(A
 // softmax, kept small: no masks on steps all of a wave's queries see, row sums
 // left per lane until the end, and the running maximum only raised (with its
 // lane exchanges and the rescaling of the output) when a score passes it by
-// more than 8 in log2 units, so p stays within 2^8 and every step in between
-// is exact relative to the same reference.  Row blocks run last to first: the
+// more than 8 in log2 units (the conditional rescaling published with
+// FlashAttention-4), so p stays within 2^8 and every step in between is exact
+// relative to the same reference.  Row blocks run last to first: the
 // ones with the most keys start first.
 // Measured per layer (the decode kernel, which streams the keys into each
 // wave's registers, before): 7B, a 2048-row chunk of ragged prompts 178 -> 80
