@@ -181,7 +181,9 @@ ROUTED = [(synth.ModelShape(1, 2048, 32, 16, 2112, 1008, "bf16"), 13, 4),   # 65
           (synth.ModelShape(1, 1536, 24, 24, 512, 1008, "bf16"), 7, 4),     # 35: O
           (synth.ModelShape(1, 1536, 24, 24, 512, 1008, "bf16"), 10, 4),    # 50: QKV and O
           (synth.ModelShape(1, 1024, 16, 16, 14336, 1008, "bf16"), 1, 4),   # 5: gate/up of 28672 columns
-          (synth.ModelShape(1, 1024, 16, 16, 14336, 1008, "bf16"), 7, 4)]   # 35
+          (synth.ModelShape(1, 1024, 16, 16, 14336, 1008, "bf16"), 7, 4),   # 35
+          (synth.ModelShape(1, 5248, 41, 41, 64, 1008, "bf16"), 3, 4),      # 15: O; QKV of 15744 columns skinny
+          (synth.ModelShape(1, 5248, 41, 41, 64, 1008, "bf16"), 4, 4)]      # 20: QKV and O
 
 
 @pytest.mark.gpu
