@@ -676,7 +676,7 @@ void* g_static_ptr[STATIC_MAX_DEV] = {};
 bool g_static_held[STATIC_MAX_DEV] = {};
 
 // The kernels' LDS limits on the current device, raised by the first context
-// there (59 attribute calls, 45 us, of some 250 us that a context takes).
+// there (59 attribute calls: 5 of the 25 us that sd_init takes).
 std::mutex g_limits_mu;
 bool g_limits_set[STATIC_MAX_DEV] = {};
 
